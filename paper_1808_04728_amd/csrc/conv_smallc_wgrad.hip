@@ -19,6 +19,7 @@
 
 #include "cf_common.h"
 #include "cf_kernels.h"
+#include "row_load.h"
 
 #include <type_traits>
 
@@ -286,8 +287,12 @@ typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));  // a plain 16
 
 // Input halo of one tile for the single-channel kernels: item (row a, b;
 // 16-byte output vector i) needs the vectors i .. i+2 of the aligned window
-// [ow0 - 8, ow0 + 40) of its input row (zeros outside the input).
-template <int KE>
+// [ow0 - 8, ow0 + 40) of its input row (zeros outside the input).  Rows of
+// whole 16-byte vectors take aligned loads; a vector of any other row may hang
+// over its end (row_load.h).  The aligned form keeps its own instantiation: the
+// end-of-row handling cost it 2.4 of 54 us at 128^3 batch 8.  Against the
+// general kernel above: 235^3 batch 2 287 -> 108 us, 37^3 batch 2 8.7 -> 5.3 us.
+template <int KE, bool ALN>
 __device__ __forceinline__ void l1_load_x(const uint16_t *__restrict__ x, const SmallcParams &p, int tid, int n,
                                           int od0, int oh0, int ow0, u32x4_t (&xv)[3]) {
   constexpr int HD = TD + KE - 1, HH = TH + KE - 1;
@@ -302,7 +307,11 @@ __device__ __forceinline__ void l1_load_x(const uint16_t *__restrict__ x, const 
 #pragma unroll
       for (int j = 0; j < 3; ++j) {
         const int iw = ow0 - 8 + 8 * (xi + j);
-        if (iw >= 0 && iw < p.w) xv[j] = *reinterpret_cast<const u32x4_t *>(x + rowoff + iw);
+        if constexpr (ALN) {
+          if (iw >= 0 && iw < p.w) xv[j] = *reinterpret_cast<const u32x4_t *>(x + rowoff + iw);
+        } else {
+          xv[j] = load_run8(x + rowoff, iw, p.w);
+        }
       }
     }
   }
@@ -331,7 +340,7 @@ __device__ __forceinline__ void l1_store_x(uint4 *xs, int tid, const u32x4_t (&x
   }
 }
 
-template <int KE, int PW>
+template <int KE, int PW, bool ALN>
 __global__ __launch_bounds__(256) void l1_wgrad_kernel(const uint16_t *__restrict__ x,
                                                        const uint16_t *__restrict__ dp,
                                                        const uint16_t *__restrict__ mask16, float alpha,
@@ -398,7 +407,7 @@ __global__ __launch_bounds__(256) void l1_wgrad_kernel(const uint16_t *__restric
     return true;
   };
   auto load_tile = [&](int n, int od0, int oh0, int ow0) {
-    l1_load_x<KE>(x, p, tid, n, od0, oh0, ow0, xv);
+    l1_load_x<KE, ALN>(x, p, tid, n, od0, oh0, ow0, xv);
     // pooled gradient: pooled voxel (pd0 + tid>>7, ph0 + (tid>>5)&3, pw0 + (tid>>1)&15), 8 channels
     dv = u32x4_t{0u, 0u, 0u, 0u};
     {
@@ -415,7 +424,7 @@ __global__ __launch_bounds__(256) void l1_wgrad_kernel(const uint16_t *__restric
       if (vd < p.od && vh < p.oh && vw < p.ow) {
         const uint16_t *mrow = mask16 + (int)__umul24(__umul24(n * p.od + vd, p.oh) + vh, p.ow);
         if (vw + 8 <= p.ow) {
-          mv = *reinterpret_cast<const u32x4_t *>(mrow + vw);
+          mv = *reinterpret_cast<const u32x4a2_t *>(mrow + vw);
         } else {
           // ragged end of a row: the voxels past it pool into no pooled voxel
           // (their B values are zero), so their bits may be anything; read only
@@ -511,7 +520,7 @@ __global__ __launch_bounds__(256) void l1_wgrad_kernel(const uint16_t *__restric
 // halves of the 64 banks.  The A side (input halo, shifted copies) and the
 // tile pipeline are those of the fused kernel above.
 // ---------------------------------------------------------------------------
-template <int KE, int PW>
+template <int KE, int PW, bool ALN>
 __global__ __launch_bounds__(256) void l1_wgrad_dz_kernel(const uint16_t *__restrict__ x,
                                                           const uint16_t *__restrict__ dz,
                                                           float *__restrict__ part_w, SmallcParams p) {
@@ -570,7 +579,7 @@ __global__ __launch_bounds__(256) void l1_wgrad_dz_kernel(const uint16_t *__rest
     return true;
   };
   auto load_tile = [&](int n, int od0, int oh0, int ow0) {
-    l1_load_x<KE>(x, p, tid, n, od0, oh0, ow0, xv);
+    l1_load_x<KE, ALN>(x, p, tid, n, od0, oh0, ow0, xv);
     const int vw = ow0 + sw;
 #pragma unroll
     for (int j = 0; j < NDZ; ++j) {
@@ -660,27 +669,25 @@ hipError_t launch_t(const ConvShape &s, const SmallcParams &p, const void *x, co
 }
 
 // the register-built-dz kernel: one input channel, 16 output channels, bf16,
-// input rows of whole 16-byte vectors, an even output width (every output
-// voxel of a row lies in a pooling window, or the row's last one does not),
-// left padding of at most one voxel
+// input rows of at least one 16-byte vector, left padding of at most one voxel
 // and index arithmetic in 24-bit products: n d h and n od oh below 2^24 (the
 // 128^3 stack at batch 8 has 2^17), every element offset below 2^31
 bool l1_supported(const ConvShape &s) {
   const long long ndh = (long long)s.n * s.d * s.h, nodoh = (long long)s.n * s.od * s.oh;
   const long long xel = ndh * s.w, mel = nodoh * s.ow * 16;
   return s.dtype == DT_BF16 && s.ci == 1 && s.co == 16 && s.sd == 1 && s.sh == 1 && s.sw == 1 && s.kd == s.kh &&
-         s.kd == s.kw && (s.kd == 2 || s.kd == 3) && s.pw <= 1 && (s.kd == 3 || s.pw == 0) && s.w % 8 == 0 &&
-         s.ow % 2 == 0 && ndh < (1LL << 24) && nodoh < (1LL << 24) && s.w < (1 << 24) && s.ow < (1 << 24) &&
+         s.kd == s.kw && (s.kd == 2 || s.kd == 3) && s.pw <= 1 && (s.kd == 3 || s.pw == 0) && s.w >= 8 &&
+         ndh < (1LL << 24) && nodoh < (1LL << 24) && s.w < (1 << 24) && s.ow < (1 << 24) &&
          xel < (1LL << 31) && mel < (1LL << 31);
 }
 
-// the unfused kernel: as l1_supported, with any output width and the dz
-// element count (16 per output voxel) below 2^31
+// the unfused kernel: as l1_supported, with the dz element count (16 per
+// output voxel) below 2^31
 bool l1_dz_supported(const ConvShape &s) {
   const long long ndh = (long long)s.n * s.d * s.h, nodoh = (long long)s.n * s.od * s.oh;
   const long long xel = ndh * s.w, zel = nodoh * s.ow * 16;
   return s.dtype == DT_BF16 && s.ci == 1 && s.co == 16 && s.sd == 1 && s.sh == 1 && s.sw == 1 && s.kd == s.kh &&
-         s.kd == s.kw && (s.kd == 2 || s.kd == 3) && s.pw <= 1 && (s.kd == 3 || s.pw == 0) && s.w % 8 == 0 &&
+         s.kd == s.kw && (s.kd == 2 || s.kd == 3) && s.pw <= 1 && (s.kd == 3 || s.pw == 0) && s.w >= 8 &&
          ndh < (1LL << 24) && nodoh < (1LL << 24) && s.w < (1 << 24) && s.ow < (1 << 24) && xel < (1LL << 31) &&
          zel < (1LL << 31);
 }
@@ -709,14 +716,15 @@ hipError_t launch_smallc_wgrad_dz(const ConvShape &s, const void *x, const void 
   const WPlan w = plan(s);
   const SmallcParams p = params(s, w);
   float *pw = (float *)ws;
+  const bool aln = s.w % 8 == 0;
   if (s.kd == 2)
-    hipLaunchKernelGGL((l1_wgrad_dz_kernel<2, 0>), dim3(w.blocks), dim3(256), 0, st, (const uint16_t *)x,
+    hipLaunchKernelGGL((aln ? l1_wgrad_dz_kernel<2, 0, true> : l1_wgrad_dz_kernel<2, 0, false>), dim3(w.blocks), dim3(256), 0, st, (const uint16_t *)x,
                        (const uint16_t *)dz, pw, p);
   else if (s.pw == 0)
-    hipLaunchKernelGGL((l1_wgrad_dz_kernel<3, 0>), dim3(w.blocks), dim3(256), 0, st, (const uint16_t *)x,
+    hipLaunchKernelGGL((aln ? l1_wgrad_dz_kernel<3, 0, true> : l1_wgrad_dz_kernel<3, 0, false>), dim3(w.blocks), dim3(256), 0, st, (const uint16_t *)x,
                        (const uint16_t *)dz, pw, p);
   else
-    hipLaunchKernelGGL((l1_wgrad_dz_kernel<3, 1>), dim3(w.blocks), dim3(256), 0, st, (const uint16_t *)x,
+    hipLaunchKernelGGL((aln ? l1_wgrad_dz_kernel<3, 1, true> : l1_wgrad_dz_kernel<3, 1, false>), dim3(w.blocks), dim3(256), 0, st, (const uint16_t *)x,
                        (const uint16_t *)dz, pw, p);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
@@ -748,14 +756,15 @@ hipError_t launch_smallc_wgrad_fused(const ConvShape &s, const void *x, const vo
   if (l1_supported(s)) {
     float *pw = (float *)ws;
     float *pb = pw + (size_t)w.blocks * M * s.co;
+    const bool aln = s.w % 8 == 0;
     if (s.kd == 2)
-      hipLaunchKernelGGL((l1_wgrad_kernel<2, 0>), dim3(w.blocks), dim3(256), 0, st, (const uint16_t *)x,
+      hipLaunchKernelGGL((aln ? l1_wgrad_kernel<2, 0, true> : l1_wgrad_kernel<2, 0, false>), dim3(w.blocks), dim3(256), 0, st, (const uint16_t *)x,
                          (const uint16_t *)dp, mask, alpha, pw, pb, p);
     else if (s.pw == 0)
-      hipLaunchKernelGGL((l1_wgrad_kernel<3, 0>), dim3(w.blocks), dim3(256), 0, st, (const uint16_t *)x,
+      hipLaunchKernelGGL((aln ? l1_wgrad_kernel<3, 0, true> : l1_wgrad_kernel<3, 0, false>), dim3(w.blocks), dim3(256), 0, st, (const uint16_t *)x,
                          (const uint16_t *)dp, mask, alpha, pw, pb, p);
     else
-      hipLaunchKernelGGL((l1_wgrad_kernel<3, 1>), dim3(w.blocks), dim3(256), 0, st, (const uint16_t *)x,
+      hipLaunchKernelGGL((aln ? l1_wgrad_kernel<3, 1, true> : l1_wgrad_kernel<3, 1, false>), dim3(w.blocks), dim3(256), 0, st, (const uint16_t *)x,
                          (const uint16_t *)dp, mask, alpha, pw, pb, p);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;

@@ -1,0 +1,131 @@
+"""First-layer kernels over extents of any parity and alignment, one and four
+input channels, against the oracle: the fused forward (pooled output and slope
+mask), the fused backward weights, non-finite inputs, and the fp32
+four-channel forward against the generic kernel bit for bit."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_1808_04728_amd import binding as B
+from tests._util import TOL, dev, maxabs_err, tdtype, to_np
+
+pytestmark = pytest.mark.gpu
+
+# N, (D,H,W), pad, alpha: widths around a tile (32, 64, 128), odd rows, incomplete pairs, the smallest extents
+CASES = [
+    (1, (8, 9, 33), "same", 0.01),
+    (2, (7, 8, 67), "valid", 0.2),     # out (5, 6, 65)
+    (1, (5, 11, 131), "same", 0.01),   # three voxels past a 128-wide tile
+    (1, (6, 17, 63), "same", 0.01),
+    (3, (4, 4, 9), "valid", 0.01),     # out (2, 2, 7)
+    (1, (9, 10, 130), "valid", 0.01),  # out (7, 8, 128), input rows of 260 bytes
+    (2, (2, 2, 8), "same", 1.5),
+    (1, (13, 26, 66), "same", 0.01),
+]
+
+
+def name(c):
+    return "n%d_%dx%dx%d_%s_a%g" % (c[0], *c[1], c[2], c[3])
+
+
+def unpack(mask, u):
+    return np.unpackbits(mask.cpu().numpy(), bitorder="little")[:u.size].astype(bool).reshape(u.shape)
+
+
+def forward(case, ci, dt, spoil=()):
+    N, dhw, pad, alpha = case
+    desc = B.make_desc(N, dhw, ci, 16, 3, 1, pad, dt)
+    assert B.cf_conv3d_fused_supported(desc) & B.FUSED_FWD
+    rng = np.random.default_rng(31)
+    xs = np.log1p(rng.poisson(np.exp(rng.standard_normal((N, *dhw, ci)))))  # many exact zeros
+    for at, v in spoil:
+        xs[at] = v
+    x = dev(xs, dt)
+    w = dev(rng.standard_normal((3, 3, 3, ci, 16)) * np.sqrt(2.0 / (27 * ci)), dt)
+    b = torch.as_tensor(rng.standard_normal(16) * 0.1, dtype=torch.float32, device="cuda")
+    od = B.cf_conv3d_out_shape(desc)
+    out = torch.full((N, *(t // 2 for t in od), 16), float("nan"), dtype=tdtype(dt), device="cuda")
+    # two guard words past the mask must stay as they are
+    nb = B.cf_conv3d_mask_bytes(desc)
+    mask = torch.full((nb + 64,), 0xA5, dtype=torch.uint8, device="cuda")
+    B.cf_conv3d_fwd_fused(desc, x, w, b, alpha, B.CF_FUSE_POOL2, out, mask)
+    torch.cuda.synchronize()
+    assert bool((mask[nb:] == 0xA5).all())
+    z = oracle.conv3d_fwd(to_np(x), to_np(w), pad=pad)
+    return out, mask, z, to_np(b), alpha
+
+
+@pytest.mark.parametrize("ci,dt", [(1, "bf16"), (4, "bf16"), (1, "f32")])
+@pytest.mark.parametrize("case", CASES, ids=name)
+def test_forward(case, ci, dt):
+    out, mask, z, b, alpha = forward(case, ci, dt)
+    u = z + b
+    assert maxabs_err(to_np(out), oracle.avgpool3d_fwd(oracle.bias_lrelu_fwd(z, b, alpha))) <= TOL[dt]
+    decided = np.abs(u) > 1e-5 * np.abs(u).max()
+    assert np.array_equal(unpack(mask, u)[decided], (u > 0)[decided])
+
+
+@pytest.mark.parametrize("value", [np.inf, -np.inf, np.nan])
+@pytest.mark.parametrize("ci", [1, 4])
+@pytest.mark.parametrize("case", [CASES[0], CASES[4], (1, (6, 7, 65), "same", 0.2)], ids=name)
+def test_forward_non_finite(case, ci, value):
+    """An infinity or NaN spoils the outputs whose window holds it and no other."""
+    dhw = case[1]
+    spoil = [((0, 1, 2, 4, ci - 1), value), ((0, dhw[0] - 1, 0, dhw[2] - 1, 0), value)]
+    out, mask, z, b, alpha = forward(case, ci, "bf16", spoil)
+    with np.errstate(invalid="ignore"):
+        u = z + b
+        p = oracle.avgpool3d_fwd(np.where(u > 0, u, alpha * u))
+        got = to_np(out)
+        fin = np.isfinite(p)
+        assert np.array_equal(np.isfinite(got), fin)
+        assert maxabs_err(got[fin], p[fin]) <= TOL["bf16"]
+        sure = np.isfinite(u) & (np.abs(u) > 1e-5 * np.abs(u[np.isfinite(u)]).max())
+        assert np.array_equal(unpack(mask, u)[sure], (u > 0)[sure])
+
+
+@pytest.mark.parametrize("ci,dt", [(1, "bf16"), (4, "bf16"), (1, "f32")])
+@pytest.mark.parametrize("case", CASES, ids=name)
+def test_backward_weights(case, ci, dt):
+    N, dhw, pad, alpha = case
+    desc = B.make_desc(N, dhw, ci, 16, 3, 1, pad, dt)
+    assert B.cf_conv3d_fused_supported(desc) & B.FUSED_BWD_WEIGHT
+    rng = np.random.default_rng(32)
+    od = B.cf_conv3d_out_shape(desc)
+    x = dev(rng.standard_normal((N, *dhw, ci)), dt)
+    g = dev(rng.standard_normal((N, *(t // 2 for t in od), 16)), dt)
+    bits = rng.integers(0, 2, (N, *od, 16)).astype(np.uint8)
+    mb = np.zeros(B.cf_conv3d_mask_bytes(desc), np.uint8)
+    packed = np.packbits(bits.reshape(-1), bitorder="little")
+    mb[:packed.size] = packed
+    mask = torch.as_tensor(mb, device="cuda")
+    dw = torch.full((3, 3, 3, ci, 16), float("nan"), device="cuda")
+    db = torch.full((16,), float("nan"), device="cuda")
+    ws = torch.empty(max(16, B.cf_conv3d_bwd_weight_fused_workspace_size(desc)), dtype=torch.uint8, device="cuda")
+    B.cf_conv3d_bwd_weight_fused(desc, x, g, mask, alpha, B.CF_FUSE_POOL2, dw, db, ws)
+    torch.cuda.synchronize()
+    dy = oracle.avgpool3d_bwd(to_np(g), od)
+    dz = dy * np.where(bits.astype(bool), 1.0, alpha)
+    # bf16: dz may be rounded once before the product (2^-9 each, over a random sum)
+    tol = 5e-3 if dt == "bf16" else TOL["f32"]
+    assert maxabs_err(to_np(dw), oracle.conv3d_bwd_weight(to_np(x), dz, 3, pad=pad)) <= tol
+    assert maxabs_err(to_np(db), dz.sum(axis=(0, 1, 2, 3))) <= 1e-5
+
+
+@pytest.mark.parametrize("pad", ["same", "valid"])
+@pytest.mark.parametrize("dhw", [(5, 9, 31), (4, 8, 32), (7, 17, 67), (3, 3, 3)])
+def test_four_channel_fp32_forward_bits(dhw, pad, monkeypatch):
+    """The plain fp32 forward adds the taps in the generic kernel's order."""
+    desc = B.make_desc(2, dhw, 4, 16, 3, 1, pad, "f32")
+    rng = np.random.default_rng(33)
+    x = dev(rng.standard_normal((2, *dhw, 4)), "f32")
+    w = dev(rng.standard_normal((3, 3, 3, 4, 16)), "f32")
+    od = B.cf_conv3d_out_shape(desc)
+    z = [torch.full((2, *od, 16), float("nan"), device="cuda") for _ in range(2)]
+    B.cf_conv3d_fwd(desc, x, w, z[0])
+    monkeypatch.setenv("CF_CONV_KERNEL", "igemm")
+    B.cf_conv3d_fwd(desc, x, w, z[1])
+    torch.cuda.synchronize()
+    assert torch.equal(z[0], z[1])
+    assert maxabs_err(to_np(z[0]), oracle.conv3d_fwd(to_np(x), to_np(w), pad=pad)) <= TOL["f32"]
