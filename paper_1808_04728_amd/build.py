@@ -35,6 +35,7 @@ COMMON = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}",
 EXTRA = {
     "conv_smallc.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
     "conv_smallc_pair.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
+    "conv_smallc4.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
     "conv_f32.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
     "conv_f32_wgrad.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
 }

@@ -542,6 +542,8 @@ cf_status cf_conv3d_fwd_fused(const cf_conv3d_desc *desc, const void *x, const v
   hipError_t e;
   if (pool && cf::l1pair_supported(s))
     e = cf::launch_l1pair_fwd(s, x, w, bias, alpha, out, (uint16_t *)mask, st);
+  else if (pool && cf::smallc_supported(s, true) && cf::l1c4_supported(s))
+    e = cf::launch_conv_fwd_l1c4(s, x, w, bias, alpha, out, (uint16_t *)mask, true, st);
   else if (pool && cf::smallc_supported(s, true))
     e = cf::launch_conv_fwd_smallc(s, x, w, bias, alpha, out, (uint16_t *)mask, true, st);
   else if (cf::f32conv_supported(s, true) && !cf::c16_fwd_supported(s))

@@ -72,6 +72,16 @@ hipError_t launch_conv_fwd_smallc(const ConvShape &s, const void *x, const void 
 bool l1pair_supported(const ConvShape &s);
 hipError_t launch_l1pair_fwd(const ConvShape &s, const void *x, const void *w, const float *bias, float alpha,
                              void *out, uint16_t *mask, hipStream_t st);
+// four input channels, 3^3, 16 outputs (conv_smallc4.hip): bf16 plain or fused
+// (pooled), fp32 plain
+bool l1c4_supported(const ConvShape &s);
+hipError_t launch_conv_fwd_l1c4(const ConvShape &s, const void *x, const void *w, const float *bias, float alpha,
+                                void *out, uint16_t *mask, bool fused, hipStream_t st);
+// its fused (pooled) backward weights in bf16 (conv_smallc4_wgrad.hip)
+bool l1c4_wgrad_supported(const ConvShape &s);
+size_t l1c4_wgrad_workspace(const ConvShape &s);
+hipError_t launch_l1c4_wgrad(const ConvShape &s, const void *x, const void *dp, const uint16_t *mask, float alpha,
+                             float *dw, float *db, void *ws, hipStream_t st);
 bool smallc_wgrad_fused_supported(const ConvShape &s);
 size_t smallc_wgrad_fused_workspace(const ConvShape &s);
 // the same layer unfused (dz given), bf16, one input channel, 16 outputs: partials in ws

@@ -579,6 +579,8 @@ static bool igemm_forced() {
 
 hipError_t launch_conv_fwd(const ConvShape &s, const void *x, const void *w, void *z,
                            hipStream_t st) {
+  // four input channels: operand fragments of whole voxels
+  if (l1c4_supported(s) && !igemm_forced()) return launch_conv_fwd_l1c4(s, x, w, nullptr, 0.f, z, nullptr, false, st);
   // few input channels: the direct halo kernel (one im2col gather per MFMA tile)
   if (smallc_supported(s, false))
     return launch_conv_fwd_smallc(s, x, w, nullptr, 0.f, z, nullptr, false, st);
