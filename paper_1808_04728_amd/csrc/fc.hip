@@ -22,6 +22,7 @@
 
 #include "cf_common.h"
 #include "cf_kernels.h"
+#include "fastdiv.h"
 
 #include <algorithm>
 
@@ -501,6 +502,7 @@ constexpr int HEAD_WT = 16384;   // weights after the first layer, rows padded b
 struct HeadParams {
   int m, L;  // batch rows, layers
   int dims[HEAD_MAX_L + 1];
+  FastDiv fd[HEAD_MAX_L + 1];  // by dims[i]
   float alpha, inv;  // inv = 1 / (m * dims[L])
   const void *w[HEAD_MAX_L];
   const float *b[HEAD_MAX_L];
@@ -513,124 +515,206 @@ struct HeadParams {
   float *loss;
 };
 
+// One 16-column tile of C[mm][n] = sum_k A[mm][k] B(k, n), mm < m <= 8, on
+// v_mfma_f32_16x16x4_f32: A rows in LDS (stride lda), B at b[k * sk + n * sn].
+// Lane l returns rows 4 (l / 16) + e of column n0 + l % 16.
+__device__ __forceinline__ f32x4_t head_tile(const float *A, int lda, int m, const float *b, int sk, int sn, int n0, int N,
+                                             int K, int lane) {
+  const int r = lane & 15, g = lane >> 4;
+  const float *ar = A + min(r, m - 1) * lda;         // rows past m repeat the last and are not used
+  const float *bc = b + min(n0 + r, N - 1) * sn;     // nor are columns past N
+  f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+  int k = 0;
+#pragma unroll 8
+  for (; k + 4 <= K; k += 4) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(ar[k + g], bc[(k + g) * sk], acc, 0, 0, 0);
+  if (k < K) {
+    const bool in = k + g < K;
+    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(in ? ar[k + g] : 0.f, in ? bc[(k + g) * sk] : 0.f, acc, 0, 0, 0);
+  }
+  return acc;
+}
+
+// One compute unit's work, so bound by its latencies: one round of global
+// loads, then a short matrix-core chain and a barrier per layer and direction
+// (the 128 x 64 layer forward: 32 MFMAs on four waves).  dz and db of a layer
+// come from the epilogue of the dx product that makes its gradient; dW is two
+// MFMAs per 16 x 16 tile.  65,536 -> 128 -> 64 -> 3, batch 8, bf16: 17.5 us as
+// one vector FMA per product with a load round per tensor, 13.9 us here (4096
+// features, batch 4: 14.1 -> 12.8; batch 1: 11.7 either way).  What is left is
+// the one workgroup's first pass through its code (its phases at 2.4 GHz: loads
+// 2.5, forward 4.5, loss 2, backward 4.4 us, for under a microsecond of matrix
+// work); barriers that do not wait for the stores did not move it, nor did
+// touching the arguments' cache lines first.
 template <int DT>
 __global__ __launch_bounds__(1024) void fc_head_tail_kernel(const HeadParams p) {
   using T = typename Store<DT>::T;
-  __shared__ float wl[HEAD_WT];         // layer i >= 1: [K][N + 1]
-  __shared__ float ys[HEAD_ACT];        // layer i: y [m][N] (fp32 values of the stored dtype)
-  __shared__ float gb[8 * HEAD_MAX_W];  // gradient of the current layer's output
-  __shared__ float zb[8 * HEAD_MAX_W];  // dz of the current layer (rounded)
-  __shared__ float red[1024];
+  __shared__ float wl[HEAD_WT];               // layer i >= 1: [K][N + 1]
+  __shared__ float ys[HEAD_ACT];              // layer i: y [m][N] (fp32 values of the stored dtype)
+  __shared__ float zb[2][8 * HEAD_MAX_W];     // dz of the current layer and the next (rounded)
+  __shared__ float red[16];
   __shared__ float bl[HEAD_MAX_L * HEAD_MAX_W];  // biases of layers 1 .. L-1
   const int tid = threadIdx.x, m = p.m, L = p.L;
+  const int lane = tid & 63, r = lane & 15, g = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const float alpha = p.alpha;
 
-  // Everything the workgroup reads from global memory, in one round: the
-  // weights of layers 1 .. L-1 (16-byte loads), their biases, the target (in
-  // zb until the loss) and layer 0's y (written by the finalize kernel).
+  // Everything the workgroup reads from global memory: layer 0's y and the
+  // target (kept in zb[1] until the loss) requested first, then layer 1's weights
+  // by twelve waves and the other layers' and the biases by four.
+  const int ny = m * p.dims[1], nt = m * p.dims[L];
+  const T y0 = tid < ny ? ((const T *)p.y[0])[tid] : from_f32<DT>(0.f);
+  const float tg = tid < nt ? p.target[tid] : 0.f;
   {
     constexpr int EV = 16 / sizeof(T);
     int off = 0;
     for (int i = 1; i < L; ++i) {
-      const int K = p.dims[i], N = p.dims[i + 1], KN = K * N, nv = KN / EV;
+      const int K = p.dims[i], N = p.dims[i + 1], KN = K * N;
       const T *w = (const T *)p.w[i];
-      for (int v = tid; v < nv; v += 1024) {
-        Vec16<DT> u;
-        u.u = ld16<false>(w + (long long)v * EV);
+      const int t0 = i == 1 ? tid : tid - 768, ts = i == 1 ? 768 : 256;
+      const bool mine = i == 1 ? tid < 768 : tid >= 768;
+      if (mine && N % EV == 0) {  // a vector lies in one row
+#pragma unroll 2
+        for (int v = t0; v < KN / EV; v += ts) {
+          Vec16<DT> u;
+          u.u = ld16<false>(w + (long long)v * EV);
+          float *d = wl + off + v * EV + fdiv(v * EV, p.fd[i + 1]);  // row pitch N + 1
 #pragma unroll
-        for (int e = 0; e < EV; ++e) {
-          const int q = v * EV + e, k = q / N, j = q - k * N;
-          wl[off + k * (N + 1) + j] = to_f32<DT>(u.e[e]);
+          for (int e = 0; e < EV; ++e) d[e] = to_f32<DT>(u.e[e]);
         }
+      } else if (mine) {
+#pragma unroll 1
+        for (int q = t0; q < KN; q += ts) wl[off + q + fdiv(q, p.fd[i + 1])] = to_f32<DT>(w[q]);
       }
-      for (int q = nv * EV + tid; q < KN; q += 1024) {
-        const int k = q / N, j = q - k * N;
-        wl[off + k * (N + 1) + j] = to_f32<DT>(w[q]);
-      }
-      for (int j = tid; j < N; j += 1024) bl[(i - 1) * HEAD_MAX_W + j] = p.b[i][j];
+      if (tid >= 768)
+#pragma unroll 1
+        for (int j = tid - 768; j < N; j += 256) bl[(i - 1) * HEAD_MAX_W + j] = p.b[i][j];
       off += K * (N + 1);
     }
-    for (int o = tid; o < m * p.dims[L]; o += 1024) zb[o] = p.target[o];
-    for (int o = tid; o < m * p.dims[1]; o += 1024) ys[o] = to_f32<DT>(((const T *)p.y[0])[o]);
   }
+  if (tid < ny) ys[tid] = to_f32<DT>(y0);
+  if (tid < nt) zb[1][tid] = tg;
+#pragma unroll 1
+  for (int o = tid + 1024; o < ny; o += 1024) ys[o] = to_f32<DT>(((const T *)p.y[0])[o]);
+#pragma unroll 1
+  for (int o = tid + 1024; o < nt; o += 1024) zb[1][o] = p.target[o];
   __syncthreads();
-  // layers 1 .. L-1 forward: z = y_prev W (k ascending), rounded; y = lrelu(z + b)
-  int yo = 0, wo = 0;
-  for (int i = 1; i < L; ++i) {
+
+  // steps 0 .. L-2: layers 1 .. L-1 forward; L-1 .. 2L-3: layers L-1 .. 1 backward.
+  // yo / wo: LDS offsets of y[i - 1] and W[i] of the step's layer
+  int yo = 0, wo = 0, cur = 0;
+#pragma unroll 1
+  for (int st = 0; st < 2 * (L - 1); ++st) {
+    const bool fw = st < L - 1;
+    const int i = fw ? st + 1 : 2 * (L - 1) - st;
     const int K = p.dims[i], N = p.dims[i + 1];
-    const int yin = yo, yout = yo + m * K;
-    for (int o = tid; o < m * N; o += 1024) {
-      const int mm = o / N, j = o - mm * N;
-      float acc = 0.f;
-#pragma unroll 16
-      for (int k = 0; k < K; ++k) acc = fmaf(ys[yin + mm * K + k], wl[wo + k * (N + 1) + j], acc);
-      const T z = from_f32<DT>(acc);
-      const float u = to_f32<DT>(z) + bl[(i - 1) * HEAD_MAX_W + j];
-      const T y = from_f32<DT>(u > 0.f ? u : alpha * u);
-      ((T *)p.y[i])[o] = y;
-      ys[yout + o] = to_f32<DT>(y);
-    }
-    yo = yout;
-    wo += K * (N + 1);
-    __syncthreads();
-  }
-  // loss = sum e^2 / (m n), dL/dy = 2 e / (m n) rounded to the dtype
-  {
-    const int n = m * p.dims[L];
-    float s = 0.f;
-    for (int o = tid; o < n; o += 1024) {
-      const float e = ys[yo + o] - zb[o];
-      s = fmaf(e, e, s);
-      gb[o] = to_f32<DT>(from_f32<DT>(2.f * e * p.inv));
-    }
-    red[tid] = s;
-    __syncthreads();  // also: the target in zb is read
-    for (int h = 512; h > 0; h >>= 1) {
-      if (tid < h) red[tid] += red[tid + h];
-      __syncthreads();
-    }
-    if (tid == 0) p.loss[0] = red[0] * p.inv;
-  }
-  // backward, layer L-1 down to 0
-  for (int i = L - 1; i >= 0; --i) {
-    const int N = p.dims[i + 1];
-    // dz = g * slope(y), rounded; db = sum over the batch rows of the unrounded products
-    for (int o = tid; o < m * N; o += 1024) {
-      const float d = gb[o] * (ys[yo + o] > 0.f ? 1.f : alpha);
-      const T dzv = from_f32<DT>(d);
-      ((T *)p.dz[i])[o] = dzv;
-      zb[o] = to_f32<DT>(dzv);
-    }
-    for (int j = tid; j < N; j += 1024) {
+    if (st == L - 1) {
+      // loss = sum e^2 / (m n); dL/dy = 2 e / (m n) rounded to the dtype; dz, db of the last layer
+      const int n = m * N;
+      const float *yl = ys + yo;
+      auto grad = [&](int o) {
+        const float e = yl[o] - zb[1][o];
+        return to_f32<DT>(from_f32<DT>(2.f * e * p.inv)) * (yl[o] > 0.f ? 1.f : alpha);
+      };
       float s = 0.f;
-#pragma unroll 8
-      for (int mm = 0; mm < m; ++mm) s += gb[mm * N + j] * (ys[yo + mm * N + j] > 0.f ? 1.f : alpha);
-      p.db[i][j] = s;
+#pragma unroll 1
+      for (int o = tid; o < n; o += 1024) {
+        const float e = yl[o] - zb[1][o];
+        s = fmaf(e, e, s);
+        const T dzv = from_f32<DT>(grad(o));
+        ((T *)p.dz[L - 1])[o] = dzv;
+        zb[0][o] = to_f32<DT>(dzv);
+      }
+#pragma unroll 1
+      for (int j = tid; j < N; j += 1024) {
+        float sb = 0.f;
+#pragma unroll 1
+        for (int mm = 0; mm < m; ++mm) sb += grad(mm * N + j);
+        p.db[L - 1][j] = sb;
+      }
+#pragma unroll
+      for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+      if (lane == 0) red[wave] = s;
+      __syncthreads();  // also: the target in zb[1] is read, dz is in zb[0]
+      if (tid == 0) {
+        float t = 0.f;
+#pragma unroll 1
+        for (int w = 0; w < 16; ++w) t += red[w];
+        p.loss[0] = t * p.inv;
+      }
+      yo -= m * K;  // back to the last layer's input and weights
+      wo -= K * (N + 1);
     }
-    __syncthreads();
-    if (i == 0) break;
-    const int K = p.dims[i];
-    const int yin = yo - m * K;
-    wo -= K * (N + 1);
-    // dW[k][j] = sum over the batch rows (ascending) of y_prev[mm][k] dz[mm][j]
-    for (int e = tid; e < K * N; e += 1024) {
-      const int k = e / N, j = e - k * N;
-      float acc = 0.f;
-#pragma unroll 8
-      for (int mm = 0; mm < m; ++mm) acc = fmaf(ys[yin + mm * K + k], zb[mm * N + j], acc);
-      p.dw[i][e] = acc;
+    // forward: z = y_prev W, y = lrelu(rounded z + b).  Backward: dx = dz W^T rounded,
+    // and from it the layer below's dz = dx * slope and db.
+    const int C = fw ? N : K, R = fw ? K : N;
+    const float *A = fw ? ys + yo : zb[cur];
+    const int yout = fw ? yo + m * K : yo;
+#pragma unroll 1
+    for (int c0 = 16 * wave; c0 < C; c0 += 256) {
+      const f32x4_t acc = head_tile(A, R, m, wl + wo, fw ? N + 1 : 1, fw ? 1 : N + 1, c0, C, R, lane);
+      const int c = c0 + r;
+      const float bias = fw && c < C ? bl[(i - 1) * HEAD_MAX_W + c] : 0.f;
+      float sb = 0.f, d[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int mm = 4 * g + e, o = mm * C + c;
+        const T v = from_f32<DT>(acc[e]);
+        const float f = to_f32<DT>(v);
+        d[e] = 0.f;
+        if (mm < m && c < C) {
+          if (fw) {
+            const float u = f + bias;
+            const T y = from_f32<DT>(u > 0.f ? u : alpha * u);
+            ((T *)p.y[i])[o] = y;
+            ys[yout + o] = to_f32<DT>(y);
+          } else {
+            ((T *)p.dx[i])[o] = v;
+            d[e] = f * (ys[yo + o] > 0.f ? 1.f : alpha);
+            const T dzv = from_f32<DT>(d[e]);
+            ((T *)p.dz[i - 1])[o] = dzv;
+            zb[cur ^ 1][o] = to_f32<DT>(dzv);
+          }
+        }
+        sb += d[e];
+      }
+      if (!fw) {
+        // db: rows 0 .. 3 in this column's first lane, then rows 4 .. 7 added in order
+        float s = __shfl(sb, r, 64);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) s += d[e];
+        if (c < C && (m > 4 ? g == 1 : g == 0)) p.db[i - 1][c] = m > 4 ? s : sb;
+      }
     }
-    // dx[mm][k] = sum over j (ascending) of dz[mm][j] W[k][j], rounded: the next g
-    for (int o = tid; o < m * K; o += 1024) {
-      const int mm = o / K, k = o - mm * K;
-      float acc = 0.f;
-#pragma unroll 16
-      for (int j = 0; j < N; ++j) acc = fmaf(zb[mm * N + j], wl[wo + k * (N + 1) + j], acc);
-      const T v = from_f32<DT>(acc);
-      ((T *)p.dx[i])[o] = v;
-      gb[o] = to_f32<DT>(v);
+    if (!fw) {
+      // dW[k][j] = sum over the batch rows of y_prev[mm][k] dz[mm][j]
+      const int tj = (N + 15) >> 4, ntl = ((K + 15) >> 4) * tj;
+#pragma unroll 1
+      for (int t = wave; t < ntl; t += 16) {
+        const int k0 = t / tj * 16, j0 = t % tj * 16;
+        const float *ya = ys + yo + min(k0 + r, K - 1), *zj = zb[cur] + min(j0 + r, N - 1);
+        f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int h = 0; h < MB; h += 4) {
+          const bool in = h + g < m;
+          const int mm = in ? h + g : 0;
+          const float a = ya[mm * K], z = zj[mm * N];
+          acc = __builtin_amdgcn_mfma_f32_16x16x4f32(in ? a : 0.f, in ? z : 0.f, acc, 0, 0, 0);
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int k = k0 + 4 * g + e, j = j0 + r;
+          if (k < K && j < N) p.dw[i][k * N + j] = acc[e];
+        }
+      }
+      cur ^= 1;
+      if (i > 1) {
+        yo -= m * p.dims[i - 1];
+        wo -= p.dims[i - 1] * (K + 1);
+      }
+    } else {
+      yo = yout;
+      wo += K * (N + 1);
     }
-    yo = yin;
     __syncthreads();
   }
 }
@@ -789,7 +873,10 @@ hipError_t launch_fc_head(int M, int L, const int *dims, int dtype, const void *
   float *part = (float *)ws;
   HeadParams hp{};
   hp.m = M; hp.L = L;
-  for (int i = 0; i <= L; ++i) hp.dims[i] = dims[i];
+  for (int i = 0; i <= L; ++i) {
+    hp.dims[i] = dims[i];
+    hp.fd[i] = make_fastdiv((uint32_t)dims[i]);
+  }
   hp.alpha = alpha;
   hp.inv = (float)(1.0 / ((double)M * dims[L]));
   for (int i = 0; i < L; ++i) {
@@ -813,13 +900,13 @@ hipError_t launch_fc_head(int M, int L, const int *dims, int dtype, const void *
     if ((e = hipGetLastError()) != hipSuccess) return e;                                                           \
     switch (G) {                                                                                                   \
       case 8: hipLaunchKernelGGL((fc_head_bwd1_kernel<DTV, 8>), dim3(blocks), dim3(256), 0, st, (const TT *)x,     \
-                                 (const TT *)dz[0], (const TT *)w[0], dw[0], (TT *)dx[0], M, K0, N1); break;       \
-      case 16: hipLaunchKernelGGL((fc_head_bwd1_kernel<DTV, 16>), dim3(blocks), dim3(256), 0, st, (const TT *)x,   \
-                                  (const TT *)dz[0], (const TT *)w[0], dw[0], (TT *)dx[0], M, K0, N1); break;      \
-      case 32: hipLaunchKernelGGL((fc_head_bwd1_kernel<DTV, 32>), dim3(blocks), dim3(256), 0, st, (const TT *)x,   \
-                                  (const TT *)dz[0], (const TT *)w[0], dw[0], (TT *)dx[0], M, K0, N1); break;      \
-      default: hipLaunchKernelGGL((fc_head_bwd1_kernel<DTV, 64>), dim3(blocks), dim3(256), 0, st, (const TT *)x,   \
-                                  (const TT *)dz[0], (const TT *)w[0], dw[0], (TT *)dx[0], M, K0, N1); break;      \
+          (const TT *)dz[0], (const TT *)w[0], dw[0], (TT *)dx[0], M, K0, N1); break;                  \
+      case 16: hipLaunchKernelGGL((fc_head_bwd1_kernel<DTV, 16>), dim3(blocks), dim3(256), 0, st, (const TT *)x,     \
+          (const TT *)dz[0], (const TT *)w[0], dw[0], (TT *)dx[0], M, K0, N1); break;                  \
+      case 32: hipLaunchKernelGGL((fc_head_bwd1_kernel<DTV, 32>), dim3(blocks), dim3(256), 0, st, (const TT *)x,     \
+          (const TT *)dz[0], (const TT *)w[0], dw[0], (TT *)dx[0], M, K0, N1); break;                  \
+      default: hipLaunchKernelGGL((fc_head_bwd1_kernel<DTV, 64>), dim3(blocks), dim3(256), 0, st, (const TT *)x,     \
+          (const TT *)dz[0], (const TT *)w[0], dw[0], (TT *)dx[0], M, K0, N1); break;                  \
     }                                                                                                              \
     return hipGetLastError();                                                                                      \
   }
