@@ -172,12 +172,23 @@ def _ptr(t):
     return t.data_ptr()
 
 
-def _stream(stream):
+_raw_current = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
+def raw_stream(stream):
+    """The hipStream_t of a torch stream, an int passed through, or (None) the
+    current stream's (asked for by handle: building torch's stream object for it
+    took 2.8 us of an 8 us call, this 0.2)."""
     if stream is None:
+        if _raw_current is not None and torch.cuda.is_initialized():
+            return _raw_current(torch._C._cuda_getDevice())
         return torch.cuda.current_stream().cuda_stream
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream
+
+
+_stream = raw_stream
 
 
 def dtype_code(dt) -> int:

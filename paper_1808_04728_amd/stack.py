@@ -30,6 +30,15 @@ def _t(dtype):
     return torch.bfloat16 if dtype == "bf16" else torch.float32
 
 
+#: bf16 stacks below this many FLOPs a step run their backward on one stream: the
+#: events and waits of a second one take the host about 25 us a layer, which only a
+#: step of 0.4 ms and more hides (six layers, one stream / two: 64^3 batch 4 199 / 236
+#: us, 96^3 batch 2 238 / 275, 128^3 batch 2 (113 GFLOP) 287 / 286, 96^3 batch 8 (190)
+#: 417 / 410, 128^3 batch 8 (475) 687 / 680; a single 64 -> 64 layer on 13^3 batch 4
+#: 65 / 73, the 32 -> 64 VALID layer on 30^3 batch 8 (124) 315 / 327)
+OVERLAP_FLOPS = 1.5e11
+
+
 class ConvStack:
     def __init__(self, layers, size, batch, dtype="f32", alpha=0.01, device="cuda", skip_first_dgrad=True,
                  fused=True, defer_reductions=True, overlap_wgrad=None, pooled_dz_pass=True, fused_from=0,
@@ -43,10 +52,9 @@ class ConvStack:
         the weight gradient on a second stream (default priority) concurrently
         with the data gradient; both only read dz (or its sources), and the
         small deep layers leave most of the GPU idle when run one after the
-        other.  None (default) = on for bf16 stacks, off for fp32 ones (measured
-        on the 128^3 stacks: bf16 batch 8 0.718 -> 0.709 ms with it; fp32 batch
-        1 0.808 -> 0.815 ms, its narrow deep-layer kernels already spread over
-        the machine).
+        other.  None (default) = on for bf16 stacks of at least OVERLAP_FLOPS a
+        step, off for smaller and for fp32 ones (128^3 fp32 batch 1 0.808 ->
+        0.815 ms, its narrow deep-layer kernels already spread over the machine).
         fused_from: layers before this index only are eligible for fusion when it
         is > 0 (an A/B switch: e.g. 2 runs the deep layers unfused).
         pooled_dz_pass: a fused pooled layer without a dz-storing weight-gradient
@@ -72,9 +80,6 @@ class ConvStack:
         self.timer = None  # optional: {op name: [(start event, end event), ...]}
         self.timed_ops = None  # None = every op, else the set of op names to time
         import torch as _torch
-        if overlap_wgrad is None:
-            overlap_wgrad = dtype == "bf16"
-        self.side = _torch.cuda.Stream(device=device) if overlap_wgrad else None
         self.L = []
         dhw = (size, size, size)
         for i, spec in enumerate(layers):
@@ -86,6 +91,10 @@ class ConvStack:
                                nvox=batch * od[0] * od[1] * od[2]))
             dhw = pdhw
         self.out_dhw = dhw
+        if overlap_wgrad is None:
+            overlap_wgrad = dtype == "bf16" and self.conv_flops() >= OVERLAP_FLOPS
+        self.side = _torch.cuda.Stream(device=device) if overlap_wgrad else None
+        self.join_event = _torch.cuda.Event() if overlap_wgrad else None
         self._alloc()
 
     # ------------------------------------------------------------------
@@ -131,6 +140,8 @@ class ConvStack:
         for i, l in enumerate(self.L):
             s = l["spec"]
             needs_dgrad = i > 0 or not self.skip_first_dgrad
+            l["side"] = self.side is not None and needs_dgrad
+            l["event"] = torch.cuda.Event() if l["side"] else None
             sup = B.cf_conv3d_fused_supported(l["desc"], B.CF_FUSE_POOL2) if s["pool"] else 0
             # fused needs both fused kernels; a layer whose data gradient is needed keeps dz
             both = B.FUSED_FWD | B.FUSED_BWD_WEIGHT
@@ -271,6 +282,7 @@ class ConvStack:
 
     # ------------------------------------------------------------------
     def forward(self, stream=None):
+        stream = B.raw_stream(stream)
         h = self.x
         for i, l in enumerate(self.L):
             s = l["spec"]
@@ -306,6 +318,8 @@ class ConvStack:
         g = dout
         pend = []
         d = self.defer_reductions
+        main = stream  # what events are recorded on (None: the current stream)
+        stream = B.raw_stream(stream)
         side_used = False
         for i in range(len(self.L) - 1, -1, -1):
             l = self.L[i]
@@ -327,7 +341,7 @@ class ConvStack:
                 else:
                     c(f"L{i+1}.pool_lrelu_bwd", B.cf_avgpool3d_lrelu_bwd, self.batch, *od, s["cout"], self.dtype, g,
                       l["mask"], self.alpha, l["dz"], l["db"], l["ws_b"], None, stream)
-                if self.side is None and s["stride"] > 1:
+                if not l["side"] and s["stride"] > 1:
                     # both plain products from dz in one call (the stride-2 layer's share
                     # one launch)
                     if d:
@@ -338,25 +352,21 @@ class ConvStack:
                           l["dw"], l["dx"], l["ws_w"], None, stream)
                     g = l["dx"]
                     continue
-                ws_ = stream
-                if self.side is not None:
-                    main = stream if stream is not None else torch.cuda.current_stream()
-                    ev = torch.cuda.Event()
-                    ev.record(main)
-                    self.side.wait_event(ev)
-                    ws_ = self.side
+                ws_, rec_ = stream, main
+                if l["side"]:
+                    ws_ = rec_ = self._fork_side(l, main)
                     side_used = True
                 if d:
                     pend += c(f"L{i+1}.conv_bwd_weight", B.cf_conv3d_bwd_weight_deferred, l["desc"],
-                              self.layer_input(i), l["dz"], l["dw"], l["ws_w"], None, ws_, rec=ws_)
+                              self.layer_input(i), l["dz"], l["dw"], l["ws_w"], None, ws_, rec=rec_)
                 else:
                     c(f"L{i+1}.conv_bwd_weight", B.cf_conv3d_bwd_weight, l["desc"], self.layer_input(i), l["dz"],
-                      l["dw"], l["ws_w"], None, ws_, rec=ws_)
+                      l["dw"], l["ws_w"], None, ws_, rec=rec_)
                 c(f"L{i+1}.conv_bwd_data", B.cf_conv3d_bwd_data, l["desc"], l["dz"], l["w"], l["dx"], stream)
                 g = l["dx"]
                 continue
             if one_stream and side_used:
-                self._join_side(stream)
+                self._join_side(main)
                 side_used = False
             if l["fused"] and l["dz_emit"]:
                 if d:
@@ -373,27 +383,23 @@ class ConvStack:
             if l["fused"]:
                 # with a fused data gradient to follow, the weight gradient goes to the
                 # side stream (both form dz from the pooled gradient and the mask)
-                ws_ = stream
-                if self.side is not None and l["dx"] is not None:
-                    main = stream if stream is not None else torch.cuda.current_stream()
-                    ev = torch.cuda.Event()
-                    ev.record(main)
-                    self.side.wait_event(ev)
-                    ws_ = self.side
+                ws_, rec_ = stream, main
+                if l["side"]:
+                    ws_ = rec_ = self._fork_side(l, main)
                     side_used = True
                 if d:
                     pend += c(f"L{i+1}.conv_bwd_weight_fused", B.cf_conv3d_bwd_weight_fused_deferred, l["desc"],
                               self.layer_input(i), g, l["mask"], self.alpha, B.CF_FUSE_POOL2, l["dw"], l["db"],
-                              None, l["ws_w"], None, ws_, rec=ws_)
+                              None, l["ws_w"], None, ws_, rec=rec_)
                 else:
                     c(f"L{i+1}.conv_bwd_weight_fused", B.cf_conv3d_bwd_weight_fused, l["desc"], self.layer_input(i),
-                      g, l["mask"], self.alpha, B.CF_FUSE_POOL2, l["dw"], l["db"], l["ws_w"], None, ws_, rec=ws_)
+                      g, l["mask"], self.alpha, B.CF_FUSE_POOL2, l["dw"], l["db"], l["ws_w"], None, ws_, rec=rec_)
                 if l["dx"] is not None:
                     c(f"L{i+1}.conv_bwd_data_fused", B.cf_conv3d_bwd_data_fused, l["desc"], g, l["mask"], l["w"],
                       self.alpha, B.CF_FUSE_POOL2, l["dx"], stream)
                     g = l["dx"]
                 continue
-            if l["fused_y"] and self.side is None and l["dx"] is not None:
+            if l["fused_y"] and not l["side"] and l["dx"] is not None:
                 # (dy, y): dW, db and dx in one call (one launch where the kernels allow)
                 if d:
                     pend += c(f"L{i+1}.conv_bwd_fused", B.cf_conv3d_bwd_fused_deferred, l["desc"],
@@ -407,21 +413,17 @@ class ConvStack:
             if l["fused_y"]:
                 # (dy, y): the weight gradient (and db) on the side stream, the data
                 # gradient on the main stream, both forming dz from dy and y
-                ws_ = stream
-                if self.side is not None and l["dx"] is not None:
-                    main = stream if stream is not None else torch.cuda.current_stream()
-                    ev = torch.cuda.Event()
-                    ev.record(main)
-                    self.side.wait_event(ev)
-                    ws_ = self.side
+                ws_, rec_ = stream, main
+                if l["side"]:
+                    ws_ = rec_ = self._fork_side(l, main)
                     side_used = True
                 if d:
                     pend += c(f"L{i+1}.conv_bwd_weight_fused", B.cf_conv3d_bwd_weight_fused_deferred, l["desc"],
                               self.layer_input(i), g, l["z"], self.alpha, 0, l["dw"], l["db"], None, l["ws_w"],
-                              None, ws_, rec=ws_)
+                              None, ws_, rec=rec_)
                 else:
                     c(f"L{i+1}.conv_bwd_weight_fused", B.cf_conv3d_bwd_weight_fused, l["desc"], self.layer_input(i),
-                      g, l["z"], self.alpha, 0, l["dw"], l["db"], l["ws_w"], None, ws_, rec=ws_)
+                      g, l["z"], self.alpha, 0, l["dw"], l["db"], l["ws_w"], None, ws_, rec=rec_)
                 if l["dx"] is not None:
                     c(f"L{i+1}.conv_bwd_data_fused", B.cf_conv3d_bwd_data_fused, l["desc"], g, l["z"], l["w"],
                       self.alpha, 0, l["dx"], stream)
@@ -433,44 +435,47 @@ class ConvStack:
                 dy = l["dy"]
             else:
                 dy = g
-            # weight gradient on the side stream when a data gradient follows
-            ws_ = stream
-            if self.side is not None and l["dx"] is not None:
-                main = stream if stream is not None else torch.cuda.current_stream()
-                ev = torch.cuda.Event()
+            # the weight gradient goes to the side stream where that pays
             if d:
                 pend += c(f"L{i+1}.bias_lrelu_bwd", B.cf_bias_lrelu_bwd_deferred, l["nvox"], s["cout"], self.dtype,
                           dy, l["z"], self.alpha, l["dz"], l["db"], l["ws_b"], None, stream)
             else:
                 c(f"L{i+1}.bias_lrelu_bwd", B.cf_bias_lrelu_bwd, l["nvox"], s["cout"], self.dtype, dy, l["z"],
                   self.alpha, l["dz"], l["db"], l["ws_b"], None, stream)
-            if self.side is not None and l["dx"] is not None:
-                ev.record(main)
-                self.side.wait_event(ev)
-                ws_ = self.side
+            ws_, rec_ = stream, main
+            if l["side"]:
+                ws_ = rec_ = self._fork_side(l, main)
                 side_used = True
             if d:
                 pend += c(f"L{i+1}.conv_bwd_weight", B.cf_conv3d_bwd_weight_deferred, l["desc"],
-                          self.layer_input(i), l["dz"], l["dw"], l["ws_w"], None, ws_, rec=ws_)
+                          self.layer_input(i), l["dz"], l["dw"], l["ws_w"], None, ws_, rec=rec_)
             else:
                 c(f"L{i+1}.conv_bwd_weight", B.cf_conv3d_bwd_weight, l["desc"], self.layer_input(i), l["dz"],
-                  l["dw"], l["ws_w"], None, ws_, rec=ws_)
+                  l["dw"], l["ws_w"], None, ws_, rec=rec_)
             if l["dx"] is not None:
                 c(f"L{i+1}.conv_bwd_data", B.cf_conv3d_bwd_data, l["desc"], l["dz"], l["w"], l["dx"], stream)
                 g = l["dx"]
         if side_used:
             # join: everything after the backward pass sees the weight gradients
-            self._join_side(stream)
+            self._join_side(main)
         if pend:
             self.reduce_bytes = sum(j.rows * j.cols * 4 + j.cols * 4 for j in pend)
             self._call("L0.reduce_partials", B.cf_reduce_partials, pend, stream)
 
+    def _fork_side(self, l, stream):
+        """The side stream, after it was made to wait for everything queued on
+        `stream` (None: the current stream) so far.  The layer's event is kept
+        between steps: making one costs more than recording it."""
+        ev = l["event"]
+        ev.record(stream)
+        self.side.wait_event(ev)
+        return self.side
+
     def _join_side(self, stream):
         """Work queued on `stream` (None: the current stream) after this call
         waits for everything queued on the side stream so far."""
-        ev = torch.cuda.Event()
-        ev.record(self.side)
-        (stream if stream is not None else torch.cuda.current_stream()).wait_event(ev)
+        self.join_event.record(self.side)
+        (stream if stream is not None else torch.cuda.current_stream()).wait_event(self.join_event)
 
     def layer_input(self, i):
         if i == 0:
