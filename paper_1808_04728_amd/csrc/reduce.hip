@@ -20,6 +20,13 @@ namespace cf {
 namespace {
 
 constexpr int MAX_JOBS = 16;
+// Loads in flight per thread: a phase's rows are a serial chain of load rounds.
+// Sixteen for narrow matrices; eight for wide ones in batches of up to 40 MB (the
+// 64^3 fp32 step's sums 10.2 -> 8.1 us, 33 MB of 45^3 partials 8.4 -> 7.3, a first
+// layer's alone 8.0 -> 5.6) and four beyond, where the machine is full anyway
+// (50 MB: 11.9 us with four, 12.5 with eight; 110 MB: 26.2 and 27.4).
+constexpr int FL_NARROW = 16, FL_WIDE = 8, FL_BIG = 4;
+constexpr long long kBigSum = 10LL << 20;  // elements
 
 struct RedJob {
   const float *part;
@@ -32,8 +39,36 @@ struct RedJob {
 
 struct RedBatch {
   int n;
+  int big;  // more than kBigSum elements in all jobs
   RedJob job[MAX_JOBS];
 };
+
+__device__ __forceinline__ void add(float4 &s, const float4 &a) {
+  s.x += a.x; s.y += a.y; s.z += a.z; s.w += a.w;
+}
+__device__ __forceinline__ void add(float &s, float a) { s += a; }
+
+// s + part[r * cols] for r = ph, ph + PH, ... < rows, added in that order, FL loads at a time
+template <int FL, class T>
+__device__ __forceinline__ T sum_phase(const T *part, int cols, int ph, int PH, int rows, T s) {
+  int r = ph;
+  for (; r + (FL - 1) * PH < rows; r += FL * PH) {
+    T a[FL];
+#pragma unroll
+    for (int u = 0; u < FL; ++u) a[u] = part[(long long)(r + u * PH) * cols];
+#pragma unroll
+    for (int u = 0; u < FL; ++u) add(s, a[u]);
+  }
+  if (r < rows) {  // the last round: loads past the end repeat its first row and are not added
+    T a[FL];
+#pragma unroll
+    for (int u = 0; u < FL; ++u) a[u] = part[(long long)(r + u * PH < rows ? r + u * PH : r) * cols];
+#pragma unroll
+    for (int u = 0; u < FL; ++u)
+      if (r + u * PH < rows) add(s, a[u]);
+  }
+  return s;
+}
 
 __global__ __launch_bounds__(256) void sum_batch_kernel(const RedBatch b) {
   __shared__ float4 red[256];
@@ -49,40 +84,13 @@ __global__ __launch_bounds__(256) void sum_batch_kernel(const RedBatch b) {
     const int cols4 = J.cols >> 2;
     const float4 *part = reinterpret_cast<const float4 *>(J.part);
     if (c < cols4) {
-      int r = ph;
-      // four independent loads per iteration, added in row order
-      for (; r + 3 * PH < rows; r += 4 * PH) {
-        const float4 a0 = part[(long long)r * cols4 + c];
-        const float4 a1 = part[(long long)(r + PH) * cols4 + c];
-        const float4 a2 = part[(long long)(r + 2 * PH) * cols4 + c];
-        const float4 a3 = part[(long long)(r + 3 * PH) * cols4 + c];
-        s.x += a0.x; s.y += a0.y; s.z += a0.z; s.w += a0.w;
-        s.x += a1.x; s.y += a1.y; s.z += a1.z; s.w += a1.w;
-        s.x += a2.x; s.y += a2.y; s.z += a2.z; s.w += a2.w;
-        s.x += a3.x; s.y += a3.y; s.z += a3.z; s.w += a3.w;
-      }
-      for (; r < rows; r += PH) {
-        const float4 a = part[(long long)r * cols4 + c];
-        s.x += a.x; s.y += a.y; s.z += a.z; s.w += a.w;
-      }
+      if (b.big) s = sum_phase<FL_BIG>(part + c, cols4, ph, PH, rows, s);
+      else s = sum_phase<FL_WIDE>(part + c, cols4, ph, PH, rows, s);
     }
   } else {
     const int cols = J.cols;
     const float *part = J.part;
-    if (c < cols) {
-      int r = ph;
-      for (; r + 3 * PH < rows; r += 4 * PH) {
-        const float a0 = part[(long long)r * cols + c];
-        const float a1 = part[(long long)(r + PH) * cols + c];
-        const float a2 = part[(long long)(r + 2 * PH) * cols + c];
-        const float a3 = part[(long long)(r + 3 * PH) * cols + c];
-        s.x += a0;
-        s.x += a1;
-        s.x += a2;
-        s.x += a3;
-      }
-      for (; r < rows; r += PH) s.x += part[(long long)r * cols + c];
-    }
+    if (c < cols) s.x = sum_phase<FL_NARROW>(part + c, cols, ph, PH, rows, s.x);
   }
   red[tid] = s;
   __syncthreads();
@@ -114,6 +122,7 @@ hipError_t launch_sum_batch(const SumJob *jobs, int n, hipStream_t st) {
   for (int b0 = 0; b0 < n; b0 += MAX_JOBS) {
     RedBatch b{};
     int blocks = 0;
+    long long elems = 0;
     for (int i = b0; i < n && b.n < MAX_JOBS; ++i) {
       const SumJob &s = jobs[i];
       if (s.cols <= 0) continue;
@@ -131,12 +140,14 @@ hipError_t launch_sum_batch(const SumJob *jobs, int n, hipStream_t st) {
       while (ph < 64 && (long long)ph * per < s.rows) ph *= 2;
       J.ph = ph;
       J.vec4 = (s.cols % 4 == 0 && s.cols >= 256 && ((uintptr_t)s.part & 15) == 0 && ((uintptr_t)s.out & 15) == 0);
+      elems += (long long)s.rows * s.cols;
       const int units = J.vec4 ? s.cols / 4 : s.cols;
       const int cpb = 256 / ph;
       J.block0 = blocks;
       blocks += (units + cpb - 1) / cpb;
     }
     if (b.n == 0) continue;
+    b.big = elems > kBigSum;
     hipLaunchKernelGGL(sum_batch_kernel, dim3(blocks), dim3(256), 0, st, b);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
