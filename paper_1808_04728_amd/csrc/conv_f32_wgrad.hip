@@ -250,7 +250,7 @@ __global__ __launch_bounds__(64 * WV) void l1_wgrad_f32_kernel(const float *__re
 }
 
 
-WPlan w_plan(const ConvShape &s, int gm) {
+WPlan w_plan(const ConvShape &s, int gm, bool pair = false) {
   const bool fused = gm == GM_POOL_MASK;  // 32 channels per workgroup (one mask word)
   WPlan pl{};
   const long long vox = (long long)s.n * s.od * s.oh * s.ow;
@@ -299,6 +299,26 @@ WPlan w_plan(const ConvShape &s, int gm) {
   // CF_F32W_TARGET overrides the workgroup target (measurement sweeps)
   if (const char *e = getenv("CF_F32W_TARGET")) target = std::max(1, atoi(e));
   long long want = std::max(1LL, (target + tiles - 1) / tiles);
+  // Short plain reductions of 4-wide kernels: half the compute units' worth of
+  // workgroups left the other half idle for the whole launch.  64k columns (32
+  // -> 64): two column groups instead of four, the same slices (22^3 VALID batch 2
+  // 79.9 -> 53.2 us, 30^3 104 -> 67, stride 2 on 32^3 33.6 -> 26.2; twice the
+  // slices instead gives 50, 64 and 31.5 us and twice the workspace).  32
+  // columns (16 -> 32): one group with the same slices below 2^14 voxels (16^3
+  // 19.0 -> 16.6, 22^3 28.7 -> 22.8), else twice the slices (32^3 54.0 -> 38.2,
+  // 37^3 81.6 -> 49.5; one group 40.1 and 59.4).  The workspace stays within the
+  // library's scratch region wherever it was.  A launch shared with the data
+  // gradient (pair) has the machine full already and keeps the wide group; its
+  // slices, and so its sums, are the same.
+  if (shortk && !fused && gm == GM_DZ && pl.kw4 && !pair && !getenv("CF_F32W_FN") && !getenv("CF_F32W_TARGET")) {
+    if (pl.fn == 4 || (pl.fn == 2 && vox < (1 << 14))) {
+      pl.fn /= 2;
+      pl.gy *= 2;
+    } else if (pl.fn == 2) {
+      const long long slice = (long long)s.kd * s.kh * s.kw * s.ci * s.co * 4, fit = (long long)kNoallocScratchBytes / slice;
+      want = want <= fit ? std::min(2 * want, std::max(fit, want)) : 2 * want;
+    }
+  }
   // CF_F32W_MINSTEPS overrides the shortest slice (measurement sweeps; 8 steps of
   // 4 voxels measured best on the stack's deep layers)
   const char *ms = getenv("CF_F32W_MINSTEPS");
@@ -372,7 +392,7 @@ hipError_t launch_wfn(const WPlan &pl, const WF32Params &p, const float *x, cons
 
 }  // namespace
 
-WPlan f32w_plan(const ConvShape &s, int gm) { return w_plan(s, gm); }
+WPlan f32w_plan(const ConvShape &s, int gm) { return w_plan(s, gm, true); }
 WF32Params f32w_params(const ConvShape &s, const WPlan &pl, float alpha) { return w_params(s, pl, alpha); }
 
 namespace {
