@@ -927,8 +927,12 @@ double f_cost(FParams &p, const FCfg &c, int fn) {
 template <int FN>
 int f_pick(const ConvShape &s, FParams &p, double *cost, bool fwd) {
   const bool four = fwd && f_tk() ? f_tk_ok(s, p) : (!fwd && FN == 1 && f_os_ok(s, p)) || f_shift_ok(s, p);
+  // a destination w row per tile (48 rows of MFMAs): from five tiles per compute
+  // unit on it beats the linear tiles (37^3, 1369 rows: 74.7 -> 58.4 us)
+  const int jw = (int)p.cls[0].fw.div;
+  const bool rowtiles = !fwd && FN == 1 && jw > 32 && jw <= 48 && f_os_ok(s, p) && p.cls[0].m / jw >= 5 * kNumCUs;
   if (four && !getenv("CF_F32_TILE") &&
-      (f_shift_env() == 1 || f_assign(p, 64) * (p.dc / (16 * FN)) >= 4 * kNumCUs)) {
+      (f_shift_env() == 1 || rowtiles || f_assign(p, 64) * (p.dc / (16 * FN)) >= 4 * kNumCUs)) {
     *cost = 0.0;
     return -1;
   }
@@ -962,6 +966,11 @@ hipError_t launch_lin(const ConvShape &s, FParams &p, const float *src, const fl
         if (64 % jw != 0) {  // a tile per destination w row
           p.rowtile = 1;
           p.cls[0].m /= (int)p.cls[0].fw.div;
+          // rows of up to 48 voxels take 48-row tiles (a quarter of a 64-row tile's
+          // MFMAs would go to idle rows: 45^3 batch 2 142.2 -> 112.7 us, 34^3 batch 4
+          // 173 -> 135)
+          if (jw <= 48)
+            return launch_f<FWD, FN, EPI, 3, 1, 1, 0, false, false, true>(p, f_assign(p, 1), src, w, bias, dst, mask, st);
           return launch_f<FWD, FN, EPI, 4, 1, 1, 0, false, false, true>(p, f_assign(p, 1), src, w, bias, dst, mask, st);
         }
         return launch_f<FWD, FN, EPI, 4, 1, 1, 0, false, false, true>(p, f_assign(p, 64), src, w, bias, dst, mask, st);

@@ -1,0 +1,72 @@
+"""fp32 launch plans of the 4-wide kernels on both sides of their size rules,
+against the oracle: backward-data with a 48- or 64-row tile per destination w
+row, and the weight gradient with narrower column groups or more slices (its
+shared launch with the data gradient gives the same bits)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_1808_04728_amd import binding as B
+from tests._util import TOL, dev, maxabs_err, to_np
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("w", [33, 47, 48, 49])
+@pytest.mark.parametrize("rows", [(3, 5), (41, 33)])  # below and above the rule's tile count (forced below)
+def test_data_gradient_row_tiles(rows, w, monkeypatch):
+    if rows == (3, 5):
+        monkeypatch.setenv("CF_F32_SHIFT", "1")
+    dhw = (*rows, w)
+    desc = B.make_desc(1, dhw, 16, 32, 4, 1, "same", "f32")
+    rng = np.random.default_rng(71)
+    dz = dev(rng.standard_normal((1, *dhw, 32)), "f32")
+    wt = dev(rng.standard_normal((4, 4, 4, 16, 32)) / 45.0, "f32")
+    dx = torch.full((1, *dhw, 16), float("nan"), device="cuda")
+    B.cf_conv3d_bwd_data(desc, dz, wt, dx)
+    torch.cuda.synchronize()
+    got = to_np(dx)
+    assert np.isfinite(got).all()
+    if rows == (3, 5):
+        assert maxabs_err(got, oracle.conv3d_bwd_data(to_np(dz), to_np(wt), dhw)) <= TOL["f32"]
+    else:  # sampled, with both ends of the rows
+        idx = np.stack([rng.integers(0, t, 400) for t in (1, *dhw, 16)], 1)
+        idx[:100, 3] = rng.integers(0, 4, 100)
+        idx[100:200, 3] = w - 1 - rng.integers(0, 4, 100)
+        ref = oracle.conv3d_bwd_data_points(to_np(dz), to_np(wt), dhw, idx)
+        assert maxabs_err(got[tuple(idx.T)], ref) <= TOL["f32"]
+
+
+# N, (D,H,W), CI, CO, stride, pad: 16 -> 32 below and from 2^14 voxels on, 32 -> 64 in both strides, one w row
+PLANS = [
+    (1, (16, 16, 63), 16, 32, 1, "same"),
+    (1, (24, 23, 31), 16, 32, 1, "same"),
+    (2, (17, 16, 16), 32, 64, 1, "valid"),
+    (1, (16, 15, 17), 32, 64, 2, "same"),
+    (1, (4, 4, 9), 32, 64, 1, "valid"),
+]
+
+
+@pytest.mark.parametrize("case", PLANS, ids=lambda c: "n%d_%dx%dx%d_c%d-%d_s%d_%s" % (c[0], *c[1], *c[2:]))
+def test_weight_gradient_plans(case):
+    N, dhw, ci, co, s, pad = case
+    desc = B.make_desc(N, dhw, ci, co, 4, s, pad, "f32")
+    od = B.cf_conv3d_out_shape(desc)
+    rng = np.random.default_rng(72)
+    x = dev(rng.standard_normal((N, *dhw, ci)), "f32")
+    dz = dev(rng.standard_normal((N, *od, co)), "f32")
+    wt = dev(rng.standard_normal((4, 4, 4, ci, co)) / 45.0, "f32")
+    ws = torch.empty(max(16, B.cf_conv3d_bwd_weight_workspace_size(desc)), dtype=torch.uint8, device="cuda")
+    dw, dw2 = torch.full_like(wt, float("nan")), torch.full_like(wt, float("nan"))
+    B.cf_conv3d_bwd_weight(desc, x, dz, dw, ws)
+    dx = torch.empty_like(x)
+    B.cf_conv3d_bwd(desc, x, dz, wt, dw2, dx, ws)
+    torch.cuda.synchronize()
+    assert torch.equal(dw, dw2)
+    # the scratch region of the call without a workspace still holds the partials
+    dw3 = torch.full_like(wt, float("nan"))
+    B.cf_conv3d_bwd_weight_noalloc(desc, x, dz, dw3)
+    torch.cuda.synchronize()
+    assert torch.equal(dw, dw3)
+    assert maxabs_err(to_np(dw), oracle.conv3d_bwd_weight(to_np(x), to_np(dz), 4, stride=s, pad=pad)) <= TOL["f32"]
