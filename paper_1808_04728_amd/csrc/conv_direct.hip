@@ -934,6 +934,13 @@ int assign_tiles(DirParams &p, int bm) {
   return 8 * slots;
 }
 
+// row tiles of bm rows in all classes
+long long count_tiles(const DirParams &p, int bm) {
+  long long tiles = 0;
+  for (int c = 0; c < p.ncls; ++c) tiles += (p.cls[c].m + bm - 1) / bm;
+  return tiles;
+}
+
 // Tile choice (measured on the deep layers of the stack): the largest row
 // tile that still yields 256 workgroups (one per compute unit); more rows per
 // wave amortise the weight stream, waves along K keep every wave busy when
@@ -942,9 +949,15 @@ int assign_tiles(DirParams &p, int bm) {
 // forward kernels (their per-step weight staging leaves load latency exposed
 // at these row counts), one for backward-data (bound by L2 -> L1 traffic,
 // where a deeper ring only adds registers) -- measured on the stack's layers.
+// Backward-data picks by cost instead: a tile's time relative to the 16-row one
+// (measured with one workgroup per compute unit: 11, 13, 16, 29 us plain, 13, 15,
+// 22, 29, 42 from (dy, y), on the 64 -> 64 layer) times the rounds of 256
+// workgroups its launch takes -- a second, nearly empty round costs a whole one
+// (13^3 batch 4 from (dy, y): 275 32-row tiles 28.8 us, 138 64-row tiles 23.7;
+// 256 -> 256 on 10^3 batch 3 33.2 -> 26.6, on 13^3 batch 4 90.0 -> 73.6).
 // CF_DIRECT_TILE="fm,wm,wk" and CF_DIRECT_PF force a variant (tests cover
 // every one this way).
-DirCfg choose_cfg(DirParams &p, int fn, bool fwd) {
+DirCfg choose_cfg(DirParams &p, int fn, bool fwd, bool dyy = false) {
   static const DirCfg cand[] = {{4, 2, 2, 1}, {2, 2, 2, 1}, {4, 1, 4, 1}, {2, 1, 4, 1}, {1, 1, 4, 1}};
   int pf = 0;
   if (const char *e = getenv("CF_DIRECT_PF")) pf = atoi(e);
@@ -961,11 +974,24 @@ DirCfg choose_cfg(DirParams &p, int fn, bool fwd) {
   }
   if (!forced) {
     const int ny = p.dc / (16 * fn);
-    for (int i = fwd ? 1 : 0; i < 5; ++i)
-      if ((long long)assign_tiles(p, 16 * cand[i].fm * cand[i].wm) * ny >= 256) {
-        pick = cand[i];
-        break;
+    if (fwd) {
+      for (int i = 1; i < 5; ++i)
+        if ((long long)assign_tiles(p, 16 * cand[i].fm * cand[i].wm) * ny >= 256) {
+          pick = cand[i];
+          break;
+        }
+    } else {
+      static const double plain[] = {2.6, 2.0, 1.47, 1.17, 1.0}, from_dyy[] = {3.2, 2.2, 1.7, 1.17, 1.0};
+      double best = 0.0;
+      for (int i = 4; i >= 0; --i) {
+        const long long wgs = count_tiles(p, 16 * cand[i].fm * cand[i].wm) * ny;
+        const double cost = (double)((wgs + kNumCUs - 1) / kNumCUs) * (dyy ? from_dyy[i] : plain[i]);
+        if (i == 4 || cost < best) {
+          best = cost;
+          pick = cand[i];
+        }
       }
+    }
   }
   if (fwd) pick.pf = 3;
   if (pf >= 1 && pf <= 3) pick.pf = pf;
@@ -993,13 +1019,19 @@ bool direct_supported(const ConvShape &s, bool fwd) {
 // LDS-staged kernel when its row tiles alone fill the machine (>= 256
 // workgroups), with 128-row tiles if they do, else 64-row tiles; 0 = the
 // register-streaming kernel.  CF_DIRECT_KERNEL=reg / lds128 / lds64 forces a
-// choice (tests cover every kernel on small shapes this way).
-int choose_lds(DirParams &p, int ny) {
+// choice (tests cover every kernel on small shapes this way).  Backward-data
+// takes it from 128 workgroups of 64-row tiles on, and 128-row tiles from 512
+// (64 -> 64 on 13^3 batch 4, 138 tiles: 21.6 -> 13.9 us; 256 -> 256 on 10^3 batch 3,
+// 188: 25.1 -> 15.3; 4096 rows, 64 tiles: 13.7 against the register kernel's 11.2;
+// 64- against 128-row tiles: 18.1 and 20.3 us on 16^3 batch 8, 133 and 125 on the
+// 30^3 VALID layer with 1688 128-row tiles).
+int choose_lds(DirParams &p, int ny, bool fwd) {
   if (const char *e = getenv("CF_DIRECT_KERNEL")) {
     if (!strcmp(e, "reg")) return 0;
     if (!strcmp(e, "lds128")) return 2;
     if (!strcmp(e, "lds64")) return 1;
   }
+  if (!fwd) return count_tiles(p, 128) * ny >= 512 ? 2 : count_tiles(p, 64) * ny >= 128 ? 1 : 0;
   if ((long long)assign_tiles(p, 128) * ny >= 256) return 2;
   if ((long long)assign_tiles(p, 64) * ny >= 256) return 1;
   return 0;
@@ -1045,7 +1077,7 @@ hipError_t launch_conv_fwd_direct(const ConvShape &s, const void *x, const void 
   DirParams p{};
   build_tables(s, true, p);
   p.alpha = alpha;
-  if (const int fm = choose_lds(p, p.dc / 64))
+  if (const int fm = choose_lds(p, p.dc / 64, true))
     return act ? launch_lds<true, 4, true>(fm, p, x, w, bias, out, mask, st)
                : launch_lds<true, 4, false>(fm, p, x, w, nullptr, out, nullptr, st);
   const DirCfg c = choose_cfg(p, 4, true);
@@ -1083,7 +1115,7 @@ hipError_t launch_conv_bwd_data_direct(const ConvShape &s, const void *dz, const
   DirParams p{};
   build_tables(s, false, p);
   const int fn = p.dc % 64 == 0 ? 4 : 2;
-  if (const int fm = choose_lds(p, p.dc / (16 * fn)))
+  if (const int fm = choose_lds(p, p.dc / (16 * fn), false))
     return fn == 4 ? launch_lds<false, 4, false>(fm, p, dz, w, nullptr, dx, nullptr, st)
                    : launch_lds<false, 2, false>(fm, p, dz, w, nullptr, dx, nullptr, st);
   const DirCfg c = choose_cfg(p, fn, false);
@@ -1119,10 +1151,10 @@ hipError_t launch_conv_bwd_data_direct_fused(const ConvShape &s, const void *g, 
   // pooled gradient: the LDS-staged kernel when its row tiles fill the machine
   // (as the plain backward-data); the register kernel otherwise and for (dy, y)
   if (gm == GRAD_POOL)
-    if (const int fm = choose_lds(p, p.dc / (16 * fn)))
+    if (const int fm = choose_lds(p, p.dc / (16 * fn), false))
       return fn == 4 ? launch_lds<false, 4, false, false, GRAD_POOL>(fm, p, g, w, nullptr, dx, nullptr, st, aux)
                      : launch_lds<false, 2, false, false, GRAD_POOL>(fm, p, g, w, nullptr, dx, nullptr, st, aux);
-  const DirCfg c = choose_cfg(p, fn, false);
+  const DirCfg c = choose_cfg(p, fn, false, gm == GRAD_DYY);
   const int tiles = assign_tiles(p, 16 * c.fm * c.wm);
   return gm == GRAD_POOL ? bwd_data_fused_t<GRAD_POOL>(c, p, tiles, fn, g, aux, w, dx, st)
                          : bwd_data_fused_t<GRAD_DYY>(c, p, tiles, fn, g, aux, w, dx, st);
