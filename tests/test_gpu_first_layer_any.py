@@ -129,3 +129,20 @@ def test_four_channel_fp32_forward_bits(dhw, pad, monkeypatch):
     torch.cuda.synchronize()
     assert torch.equal(z[0], z[1])
     assert maxabs_err(to_np(z[0]), oracle.conv3d_fwd(to_np(x), to_np(w), pad=pad)) <= TOL["f32"]
+
+
+@pytest.mark.parametrize("dhw,pad,k", [((7, 9, 33), "same", 3), ((5, 8, 67), "valid", 3), ((6, 5, 13), "same", 2),
+                                       ((4, 4, 9), "valid", 3), ((3, 6, 8), "same", 3)])
+def test_plain_backward_weights_one_channel(dhw, pad, k):
+    """The unfused bf16 kernel (dz from memory) over the same kinds of rows."""
+    desc = B.make_desc(2, dhw, 1, 16, k, 1, pad, "bf16")
+    od = B.cf_conv3d_out_shape(desc)
+    rng = np.random.default_rng(34)
+    x = dev(rng.standard_normal((2, *dhw, 1)), "bf16")
+    dz = dev(rng.standard_normal((2, *od, 16)), "bf16")
+    dw = torch.full((k, k, k, 1, 16), float("nan"), device="cuda")
+    ws = torch.empty(max(16, B.cf_conv3d_bwd_weight_workspace_size(desc)), dtype=torch.uint8, device="cuda")
+    B.cf_conv3d_bwd_weight(desc, x, dz, dw, ws)
+    torch.cuda.synchronize()
+    # exact products, fp32 sums of a few thousand terms
+    assert maxabs_err(to_np(dw), oracle.conv3d_bwd_weight(to_np(x), to_np(dz), k, pad=pad)) <= 1e-5
