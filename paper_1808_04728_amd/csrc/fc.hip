@@ -573,13 +573,23 @@ __global__ __launch_bounds__(1024) void fc_head_tail_kernel(const HeadParams p) 
       const int t0 = i == 1 ? tid : tid - 768, ts = i == 1 ? 768 : 256;
       const bool mine = i == 1 ? tid < 768 : tid >= 768;
       if (mine && N % EV == 0) {  // a vector lies in one row
-#pragma unroll 2
-        for (int v = t0; v < KN / EV; v += ts) {
-          Vec16<DT> u;
-          u.u = ld16<false>(w + (long long)v * EV);
-          float *d = wl + off + v * EV + fdiv(v * EV, p.fd[i + 1]);  // row pitch N + 1
+        // 128 x 64 in one round of loads, two (bf16) or three (fp32) a thread: the whole
+        // fp32 head at 6656 features, batch 1, 25.9 -> 25.4 us against a loop of two
+        constexpr int NB = DT == DT_F32 ? 3 : 2;
+        const int nv = KN / EV;
+#pragma unroll 1
+        for (int v0 = t0; v0 < nv; v0 += NB * ts) {
+          Vec16<DT> u[NB];
 #pragma unroll
-          for (int e = 0; e < EV; ++e) d[e] = to_f32<DT>(u.e[e]);
+          for (int b = 0; b < NB; ++b) u[b].u = ld16<false>(w + (long long)min(v0 + b * ts, nv - 1) * EV);
+#pragma unroll
+          for (int b = 0; b < NB; ++b) {
+            const int v = v0 + b * ts;
+            if (v >= nv) break;
+            float *d = wl + off + v * EV + fdiv(v * EV, p.fd[i + 1]);  // row pitch N + 1
+#pragma unroll
+            for (int e = 0; e < EV; ++e) d[e] = to_f32<DT>(u[b].e[e]);
+          }
         }
       } else if (mine) {
 #pragma unroll 1
