@@ -35,8 +35,9 @@ def _t(dtype):
 #: step of 0.4 ms and more hides (six layers, one stream / two: 64^3 batch 4 199 / 236
 #: us, 96^3 batch 2 238 / 275, 128^3 batch 2 (113 GFLOP) 287 / 286, 96^3 batch 8 (190)
 #: 417 / 410, 128^3 batch 8 (475) 687 / 680; a single 64 -> 64 layer on 13^3 batch 4
-#: 65 / 73, the 32 -> 64 VALID layer on 30^3 batch 8 (124) 315 / 327)
-OVERLAP_FLOPS = 1.5e11
+#: 65 / 73, the 32 -> 64 VALID layer on 30^3 batch 8 (124) 315 / 327; 120^3 batch 3 (147)
+#: 349 / 341, so the line lies between that layer on 31^3 (138) and this step)
+OVERLAP_FLOPS = 1.4e11
 
 
 class ConvStack:
