@@ -922,15 +922,18 @@ double f_cost(FParams &p, const FCfg &c, int fn) {
   return rounds * (steps * 4.0 * c.fm * fn + 200.0);
 }
 
-// The tile of a linear-layout launch: shift mode (pick -1) for the large
-// stride-1 4-wide layers, else the candidate of least cost.
+// The tile of a linear-layout launch: a four-tap mode (pick -1: taps in K, output
+// shift or shift mode) for the large stride-1 4-wide layers, else the candidate of
+// least cost.  Output shift reads a stored dz: the (dy, y) form (dyy) has shift
+// mode alone, and so only on w extents that are multiples of 16.
 template <int FN>
-int f_pick(const ConvShape &s, FParams &p, double *cost, bool fwd) {
-  const bool four = fwd && f_tk() ? f_tk_ok(s, p) : (!fwd && FN == 1 && f_os_ok(s, p)) || f_shift_ok(s, p);
+int f_pick(const ConvShape &s, FParams &p, double *cost, bool fwd, bool dyy) {
+  const bool os = !fwd && !dyy && FN == 1 && f_os_ok(s, p);
+  const bool four = fwd && f_tk() ? f_tk_ok(s, p) : os || f_shift_ok(s, p);
   // a destination w row per tile (48 rows of MFMAs): from five tiles per compute
   // unit on it beats the linear tiles (37^3, 1369 rows: 74.7 -> 58.4 us)
   const int jw = (int)p.cls[0].fw.div;
-  const bool rowtiles = !fwd && FN == 1 && jw > 32 && jw <= 48 && f_os_ok(s, p) && p.cls[0].m / jw >= 5 * kNumCUs;
+  const bool rowtiles = os && jw > 32 && jw <= 48 && p.cls[0].m / jw >= 5 * kNumCUs;
   if (four && !getenv("CF_F32_TILE") &&
       (f_shift_env() == 1 || rowtiles || f_assign(p, 64) * (p.dc / (16 * FN)) >= 4 * kNumCUs)) {
     *cost = 0.0;
@@ -955,7 +958,7 @@ template <bool FWD, int FN, int EPI, bool DYY = false>
 hipError_t launch_lin(const ConvShape &s, FParams &p, const float *src, const float *w, const float *bias, float *dst,
                       uint8_t *mask, hipStream_t st, const float *ysrc = nullptr) {
   double cost;
-  const int pick = f_pick<FN>(s, p, &cost, FWD);
+  const int pick = f_pick<FN>(s, p, &cost, FWD, DYY);
   if (pick < 0) {
     if constexpr (FWD && !DYY) {
       if (f_tk()) return launch_f<FWD, FN, EPI, 4, 1, 1, 0, false, true>(p, f_assign(p, 64), src, w, bias, dst, mask, st);
@@ -976,6 +979,7 @@ hipError_t launch_lin(const ConvShape &s, FParams &p, const float *src, const fl
         return launch_f<FWD, FN, EPI, 4, 1, 1, 0, false, false, true>(p, f_assign(p, 64), src, w, bias, dst, mask, st);
       }
     }
+    if (!f_shift_ok(s, p)) return hipErrorInvalidValue;  // f_pick chose a mode this form does not have
     return launch_f<FWD, FN, EPI, 4, 1, 1, 4, DYY>(p, f_assign(p, 64), src, w, bias, dst, mask, st, ysrc);
   }
   const FCfg c = kCand[pick];
@@ -1000,7 +1004,7 @@ hipError_t launch_lin(const ConvShape &s, FParams &p, const float *src, const fl
 // the small deep layers (a few hundred rows at batch 1) several times more
 // workgroups, each with a share of the columns, instead of a few dozen that
 // leave most compute units idle.  CF_F32_FN=1|2|4 forces a width.
-int f_pick_fn(const ConvShape &s, FParams &p, int fnmax, bool fwd) {
+int f_pick_fn(const ConvShape &s, FParams &p, int fnmax, bool fwd, bool dyy = false) {
   if (const char *e = getenv("CF_F32_FN")) {
     const int f = atoi(e);
     if ((f == 1 || f == 2 || f == 4) && f <= fnmax && p.dc % (16 * f) == 0) return f;
@@ -1010,7 +1014,9 @@ int f_pick_fn(const ConvShape &s, FParams &p, int fnmax, bool fwd) {
   for (int f = fnmax; f >= 1; f >>= 1) {
     if (p.dc % (16 * f) != 0) continue;
     double c;
-    const int pick = f == 4 ? f_pick<4>(s, p, &c, fwd) : f == 2 ? f_pick<2>(s, p, &c, fwd) : f_pick<1>(s, p, &c, fwd);
+    const int pick = f == 4   ? f_pick<4>(s, p, &c, fwd, dyy)
+                     : f == 2 ? f_pick<2>(s, p, &c, fwd, dyy)
+                              : f_pick<1>(s, p, &c, fwd, dyy);
     if (pick < 0) return fnmax;  // shift mode: the large layers keep the widest groups
     if (f == fnmax || c < best) {
       best = c;
@@ -1168,13 +1174,14 @@ hipError_t launch_pair(const ConvShape &s, const WPlan &wpl, FParams &fp, const 
 
 // the backward-data plan, as launch_conv_bwd_data_f32 makes it: column groups
 // and the kCand tile (-1 for the shift / output-shift modes)
-int dgrad_plan(const ConvShape &s, FParams &fp, float alpha, int *fn) {
+int dgrad_plan(const ConvShape &s, FParams &fp, float alpha, bool dyy, int *fn) {
   f_tables(s, false, fp);
   fp.alpha = alpha;
-  *fn = f_pick_fn(s, fp, s.ci % 64 == 0 ? 4 : (s.ci % 32 == 0 ? 2 : 1), false);
+  *fn = f_pick_fn(s, fp, s.ci % 64 == 0 ? 4 : (s.ci % 32 == 0 ? 2 : 1), false, dyy);
   double cost = 0.0;
-  return *fn == 1 ? f_pick<1>(s, fp, &cost, false) : *fn == 2 ? f_pick<2>(s, fp, &cost, false)
-                                                              : f_pick<4>(s, fp, &cost, false);
+  return *fn == 1   ? f_pick<1>(s, fp, &cost, false, dyy)
+         : *fn == 2 ? f_pick<2>(s, fp, &cost, false, dyy)
+                    : f_pick<4>(s, fp, &cost, false, dyy);
 }
 }  // namespace
 
@@ -1183,7 +1190,7 @@ hipError_t launch_conv_bwd_fused_f32(const ConvShape &s, const float *x, const f
                                      hipStream_t st) {
   FParams fp{};
   int fn = 0;
-  const int pick = dgrad_plan(s, fp, alpha, &fn);
+  const int pick = dgrad_plan(s, fp, alpha, true, &fn);
   const WPlan wpl = f32w_plan(s, GM_DY_Y);
   if (fn == 1 && pick == 6 && !wpl.kw4 && wpl.ru == 1 && wpl.fn >= 2 && s.co % 32 == 0 && pair_env())
     return launch_pair<GM_DY_Y, false, 8, 2, 1, 1, 1, 8, true, 4>(s, wpl, fp, x, dy, y, w, alpha, dw, db, dx, ws, st);
@@ -1196,7 +1203,7 @@ hipError_t launch_conv_bwd_f32(const ConvShape &s, const float *x, const float *
                                float *dx, void *ws, hipStream_t st) {
   FParams fp{};
   int fn = 0;
-  const int pick = dgrad_plan(s, fp, 0.f, &fn);
+  const int pick = dgrad_plan(s, fp, 0.f, false, &fn);
   const WPlan wpl = f32w_plan(s, GM_DZ);
   if (fn == 2 && pick == 3 && wpl.kw4 && wpl.ru == 1 && wpl.fn == 4 && pair_env())
     return launch_pair<GM_DZ, true, 4, 4, 2, 4, 1, 4, false, 3>(s, wpl, fp, x, dz, nullptr, w, 0.f, dw, nullptr, dx, ws,
@@ -1211,7 +1218,7 @@ hipError_t launch_conv_bwd_data_f32(const ConvShape &s, const float *dz, const f
   FParams p{};
   f_tables(s, false, p);
   p.alpha = alpha;
-  const int fn = f_pick_fn(s, p, s.ci % 64 == 0 ? 4 : (s.ci % 32 == 0 ? 2 : 1), false);
+  const int fn = f_pick_fn(s, p, s.ci % 64 == 0 ? 4 : (s.ci % 32 == 0 ? 2 : 1), false, y != nullptr);
   if (y) {
     if (fn == 4) return launch_lin<false, 4, 0, true>(s, p, dz, w, nullptr, dx, nullptr, st, y);
     if (fn == 2) return launch_lin<false, 2, 0, true>(s, p, dz, w, nullptr, dx, nullptr, st, y);

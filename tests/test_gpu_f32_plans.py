@@ -70,3 +70,39 @@ def test_weight_gradient_plans(case):
     torch.cuda.synchronize()
     assert torch.equal(dw, dw3)
     assert maxabs_err(to_np(dw), oracle.conv3d_bwd_weight(to_np(x), to_np(dz), 4, stride=s, pad=pad)) <= TOL["f32"]
+
+
+@pytest.mark.parametrize("w", [33, 37, 47, 50])
+@pytest.mark.parametrize("rows", [(3, 5), (41, 33)])  # below and above the plain form's size rules (forced below)
+def test_data_gradient_from_dy_and_y(rows, w, monkeypatch):
+    """An unpooled 4-wide layer's data gradient from (dy, y) on w rows that no
+    16-voxel fragment divides: it has the linear tiles alone, whatever modes
+    the plain form (dz given) takes at the same sizes."""
+    if rows == (3, 5):
+        monkeypatch.setenv("CF_F32_SHIFT", "1")
+    dhw = (*rows, w)
+    desc = B.make_desc(1, dhw, 16, 32, 4, 1, "same", "f32")
+    assert B.cf_conv3d_fused_supported(desc, 0) & B.FUSED_BWD_DATA
+    rng = np.random.default_rng(73)
+    dy = dev(rng.standard_normal((1, *dhw, 32)), "f32")
+    y = dev(rng.standard_normal((1, *dhw, 32)), "f32")
+    x = dev(rng.standard_normal((1, *dhw, 16)), "f32")
+    wt = dev(rng.standard_normal((4, 4, 4, 16, 32)) / 45.0, "f32")
+    dx, dx1 = torch.full_like(x, float("nan")), torch.full_like(x, float("nan"))
+    B.cf_conv3d_bwd_data_fused(desc, dy, y, wt, 0.2, 0, dx)
+    dw, db = torch.empty_like(wt), torch.empty(32, device="cuda")
+    ws = torch.empty(B.cf_conv3d_bwd_weight_fused_workspace_size(desc, 0), dtype=torch.uint8, device="cuda")
+    B.cf_conv3d_bwd_fused(desc, x, dy, y, wt, 0.2, 0, dw, db, dx1, ws)
+    torch.cuda.synchronize()
+    assert torch.equal(dx, dx1)
+    dz, _ = oracle.bias_lrelu_bwd(to_np(dy), to_np(y), 0.2)
+    got = to_np(dx)
+    assert np.isfinite(got).all()
+    if rows == (3, 5):
+        assert maxabs_err(got, oracle.conv3d_bwd_data(dz, to_np(wt), dhw)) <= TOL["f32"]
+    else:
+        idx = np.stack([rng.integers(0, t, 400) for t in (1, *dhw, 16)], 1)
+        idx[:100, 3] = rng.integers(0, 4, 100)
+        idx[100:200, 3] = w - 1 - rng.integers(0, 4, 100)
+        ref = oracle.conv3d_bwd_data_points(dz, to_np(wt), dhw, idx)
+        assert maxabs_err(got[tuple(idx.T)], ref) <= TOL["f32"]
