@@ -146,3 +146,72 @@ def test_plain_backward_weights_one_channel(dhw, pad, k):
     torch.cuda.synchronize()
     # exact products, fp32 sums of a few thousand terms
     assert maxabs_err(to_np(dw), oracle.conv3d_bwd_weight(to_np(x), to_np(dz), k, pad=pad)) <= 1e-5
+
+
+def gradient(case, ci, dt, spoil_x=(), spoil_g=(), keep=0.5):
+    """The fused backward weights of a positive input, with the oracle's dz."""
+    N, dhw, pad, alpha = case
+    desc = B.make_desc(N, dhw, ci, 16, 3, 1, pad, dt)
+    rng = np.random.default_rng(35)
+    od = B.cf_conv3d_out_shape(desc)
+    xs = 0.1 + np.abs(rng.standard_normal((N, *dhw, ci)))
+    gs = 0.1 + np.abs(rng.standard_normal((N, *(t // 2 for t in od), 16)))
+    for at, v in spoil_x:
+        xs[at] = v
+    for at, v in spoil_g:
+        gs[at] = v
+    x, g = dev(xs, dt), dev(gs, dt)
+    bits = (rng.random((N, *od, 16)) < keep).astype(np.uint8)
+    mb = np.zeros(B.cf_conv3d_mask_bytes(desc), np.uint8)
+    packed = np.packbits(bits.reshape(-1), bitorder="little")
+    mb[:packed.size] = packed
+    dw = torch.full((3, 3, 3, ci, 16), float("nan"), device="cuda")
+    db = torch.full((16,), float("nan"), device="cuda")
+    ws = torch.empty(max(16, B.cf_conv3d_bwd_weight_fused_workspace_size(desc)), dtype=torch.uint8, device="cuda")
+    B.cf_conv3d_bwd_weight_fused(desc, x, g, torch.as_tensor(mb, device="cuda"), alpha, B.CF_FUSE_POOL2, dw, db, ws)
+    torch.cuda.synchronize()
+    with np.errstate(invalid="ignore"):
+        dz = oracle.avgpool3d_bwd(to_np(g), od) * np.where(bits.astype(bool), 1.0, alpha)
+        return to_np(dw), to_np(db), oracle.conv3d_bwd_weight(to_np(x), dz, 3, pad=pad), dz.sum(axis=(0, 1, 2, 3))
+
+
+def same_class(got, ref, tol):
+    """NaN and the infinities where the reference has them, the rest within tol of its largest."""
+    inf, fin = np.isinf(ref), np.isfinite(ref)
+    nan_alike = np.array_equal(np.isnan(got), np.isnan(ref))
+    inf_alike = np.array_equal(np.isinf(got), inf) and np.array_equal(got[inf], ref[inf])
+    assert nan_alike and inf_alike
+    assert maxabs_err(got[fin], ref[fin]) <= tol
+
+
+@pytest.mark.parametrize("alpha", [0.0, 0.01, 1.0, 3.0])
+@pytest.mark.parametrize("ci,dt,w", [(1, "bf16", 33), (1, "bf16", 40), (1, "f32", 33), (1, "f32", 40)])
+def test_backward_weights_infinite_gradient(ci, dt, w, alpha):
+    """An infinite pooled gradient inside the volume: its channel's sums are
+    infinite (NaN where the slope alpha = 0 meets it), every other sum is as
+    without it."""
+    for keep in (1.0, 0.5):
+        spoil = [((0, 1, 1, 2, 3), np.inf), ((0, 1, 2, 9, 7), -np.inf)]
+        dw, db, rw, rb = gradient((1, (6, 8, w), "same", alpha), ci, dt, spoil_g=spoil, keep=keep)
+        assert np.isinf(rb[3]) or alpha == 0.0
+        same_class(dw, rw, 5e-3 if dt == "bf16" else TOL["f32"])
+        same_class(db, rb, 1e-5)
+
+
+@pytest.mark.parametrize("alpha", [0.01, 3.0])
+@pytest.mark.parametrize("ci,dt,w", [(1, "bf16", 33), (1, "f32", 33)])
+def test_backward_weights_infinite_input(ci, dt, w, alpha):
+    """An infinite input voxel whose windows all lie in the pooled volume."""
+    dw, db, rw, rb = gradient((1, (6, 8, w), "same", alpha), ci, dt, spoil_x=[((0, 2, 3, 7, ci - 1), np.inf)])
+    assert np.isinf(rw[:, :, :, ci - 1]).all()
+    same_class(dw, rw, 5e-3 if dt == "bf16" else TOL["f32"])
+    same_class(db, rb, 1e-5)
+
+
+@pytest.mark.parametrize("ci,dt,w", [(1, "bf16", 33), (1, "bf16", 40), (1, "f32", 33)])
+def test_backward_weights_steep_slope(ci, dt, w):
+    """A slope far above 1 that no voxel takes: the kept voxels' sums must not
+    drown in the rounding of alpha times all."""
+    dw, db, rw, rb = gradient((1, (6, 8, w), "same", 4e6), ci, dt, keep=1.0)
+    same_class(dw, rw, 5e-3 if dt == "bf16" else TOL["f32"])
+    same_class(db, rb, 1e-5)
