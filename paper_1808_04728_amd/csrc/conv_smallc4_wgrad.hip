@@ -20,7 +20,12 @@
 //      picks one of them per voxel (one bit select per pair).  This is the
 //      bf16 rounding of dz times 8.
 // db is summed from the unrounded values: a fragment of ones times g and times
-// the masked g, combined as alpha / 8 and (1 - alpha) / 8.
+// the masked g, combined as alpha / 8 and (1 - alpha) / 8.  For a slope above 1
+// that is a difference of large terms (and of infinities), for a slope of 0 an
+// infinity of g meets the factor 0: there the workgroups whose sums call for it
+// add up their dz once more, voxel by voxel (DEF, an instantiation of its own:
+// its registers cost 1 to 2% of the launch, 128^3 batch 2 38.3 -> 39.1 us, and
+// the pass itself 22% at a slope of 3).
 //
 // 256^3 batch 2: 1374 us with the general kernel (shifted copies built element
 // by element, 79 KB of LDS), 235-252 us here.  Four workgroups per compute unit
@@ -54,6 +59,7 @@ __device__ __forceinline__ u32x2_t tr4(const unsigned char *p) {
   return __builtin_bit_cast(u32x2_t, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16_t *)p));
 }
 
+template <bool DEF>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) void l1c4_wgrad_kernel(
     const uint16_t *__restrict__ x, const uint16_t *__restrict__ dp, const uint16_t *__restrict__ mask16, float alpha,
     float *__restrict__ part_w, float *__restrict__ part_b, SmallcParams p, C4Tiles tiles, int total_tiles) {
@@ -197,7 +203,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
   }
 
   // ---- combine the four waves: acc[k][e] = row (kernel row k, kw = q, ci = e), column r
-  const float cu = alpha == 0.f ? 0.f : 0.5f * alpha, cm = 0.125f * (1.f - alpha);
+  const float cu = 0.5f * alpha, cm = 0.125f * (1.f - alpha);
   float (*const red)[M + 1][16] = reinterpret_cast<float (*)[M + 1][16]>(smem);
   if (q < 3) {
 #pragma unroll
@@ -206,14 +212,45 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
       for (int e = 0; e < 4; ++e) red[wave][(k * 3 + q) * 4 + e][r] = 0.125f * acc[k][e];
   } else {
     // four voxel rows share one product of ones with g
-    red[wave][M][r] = (alpha == 0.f ? 0.f : cu * acc_u[0]) + (alpha == 1.f ? 0.f : cm * acc_m[0]);
+    red[wave][M][r] = cu * acc_u[0] + (alpha == 1.f ? 0.f : cm * acc_m[0]);
   }
   __syncthreads();
+  // every wave looks at all 64 sums of db: the workgroup takes one way
+  const bool by_def =
+      DEF && (alpha > 1.f || __builtin_amdgcn_ballot_w64(!(fabsf(red[lane >> 4][M][lane & 15]) < __builtin_inff())));
   for (int i = tid; i < (M + 1) * 16; i += 256) {
     const int row = i >> 4, co = i & 15;
     const float v = red[0][row][co] + red[1][row][co] + red[2][row][co] + red[3][row][co];
     if (row < M) part_w[(long long)blockIdx.x * M * 16 + i] = v;
-    else part_b[(long long)blockIdx.x * 16 + co] = v;
+    else if (!by_def) part_b[(long long)blockIdx.x * 16 + co] = v;
+  }
+  if (by_def) {  // (uniform)
+    float sb[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    // thread: the pooled voxel and channel half it loads in load_tile
+    for (int t = xcd * per + wg; t < tend; t += nwg) {
+      const C4Tile tl = c4_tile(t, tiles, TW);
+      const int pd_ = (tl.d >> 1) + (tid >> 7), ph_ = (tl.h >> 1) + ((tid >> 5) & 3), pw_ = (tl.w >> 1) + ((tid >> 1) & 15);
+      if (pd_ >= p.pod || ph_ >= p.poh || pw_ >= p.pow_) continue;
+      const uint16_t *g =
+          dp + ((((long long)tl.n * p.pod + pd_) * p.poh + ph_) * p.pow_ + pw_) * 16 + 8 * (tid & 1);
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        const int vd = 2 * pd_ + (k >> 2), vh = 2 * ph_ + ((k >> 1) & 1), vw = 2 * pw_ + (k & 1);
+        const uint32_t bits = mask16[(((long long)tl.n * p.od + vd) * p.oh + vh) * p.ow + vw] >> (8 * (tid & 1));
+#pragma unroll
+        for (int j = 0; j < 8; ++j) sb[j] += bf2f(g[j]) * 0.125f * ((bits >> j & 1u) ? 1.f : alpha);
+      }
+    }
+    __syncthreads();  // every wave has read its sums
+    float *const sums = reinterpret_cast<float *>(smem);  // [128 pooled voxels][16 channels]
+#pragma unroll
+    for (int j = 0; j < 8; ++j) sums[(tid >> 1) * 16 + 8 * (tid & 1) + j] = sb[j];
+    __syncthreads();
+    if (tid < 16) {
+      float v = 0.f;
+      for (int k = 0; k < 128; ++k) v += sums[k * 16 + tid];
+      part_b[(long long)blockIdx.x * 16 + tid] = v;
+    }
   }
 }
 
@@ -239,8 +276,9 @@ hipError_t launch_l1c4_wgrad(const ConvShape &s, const void *x, const void *dp, 
   const C4Tiles tiles = c4_tiles(s, TW, &total);
   const int blocks = c4_blocks(s);
   float *pw = (float *)ws, *pb = pw + (size_t)blocks * M * 16;
-  hipLaunchKernelGGL(l1c4_wgrad_kernel, dim3(blocks), dim3(256), 0, st, (const uint16_t *)x, (const uint16_t *)dp, mask,
-                     alpha, pw, pb, c4_params(s), tiles, (int)total);
+  const bool def = alpha == 0.f || alpha > 1.f;
+  hipLaunchKernelGGL((def ? l1c4_wgrad_kernel<true> : l1c4_wgrad_kernel<false>), dim3(blocks), dim3(256), 0, st,
+                     (const uint16_t *)x, (const uint16_t *)dp, mask, alpha, pw, pb, c4_params(s), tiles, (int)total);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   e = launch_sum_rows(pw, dw, blocks, M * 16, st);

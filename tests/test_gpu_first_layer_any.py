@@ -185,7 +185,7 @@ def same_class(got, ref, tol):
 
 
 @pytest.mark.parametrize("alpha", [0.0, 0.01, 1.0, 3.0])
-@pytest.mark.parametrize("ci,dt,w", [(1, "bf16", 33), (1, "bf16", 40), (1, "f32", 33), (1, "f32", 40)])
+@pytest.mark.parametrize("ci,dt,w", [(1, "bf16", 33), (1, "bf16", 40), (4, "bf16", 33), (1, "f32", 33), (1, "f32", 40)])
 def test_backward_weights_infinite_gradient(ci, dt, w, alpha):
     """An infinite pooled gradient inside the volume: its channel's sums are
     infinite (NaN where the slope alpha = 0 meets it), every other sum is as
@@ -199,7 +199,7 @@ def test_backward_weights_infinite_gradient(ci, dt, w, alpha):
 
 
 @pytest.mark.parametrize("alpha", [0.01, 3.0])
-@pytest.mark.parametrize("ci,dt,w", [(1, "bf16", 33), (1, "f32", 33)])
+@pytest.mark.parametrize("ci,dt,w", [(1, "bf16", 33), (4, "bf16", 33), (1, "f32", 33)])
 def test_backward_weights_infinite_input(ci, dt, w, alpha):
     """An infinite input voxel whose windows all lie in the pooled volume."""
     dw, db, rw, rb = gradient((1, (6, 8, w), "same", alpha), ci, dt, spoil_x=[((0, 2, 3, 7, ci - 1), np.inf)])
@@ -208,7 +208,7 @@ def test_backward_weights_infinite_input(ci, dt, w, alpha):
     same_class(db, rb, 1e-5)
 
 
-@pytest.mark.parametrize("ci,dt,w", [(1, "bf16", 33), (1, "bf16", 40), (1, "f32", 33)])
+@pytest.mark.parametrize("ci,dt,w", [(1, "bf16", 33), (1, "bf16", 40), (4, "bf16", 33), (1, "f32", 33)])
 def test_backward_weights_steep_slope(ci, dt, w):
     """A slope far above 1 that no voxel takes: the kept voxels' sums must not
     drown in the rounding of alpha times all."""
