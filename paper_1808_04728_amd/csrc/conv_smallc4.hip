@@ -13,9 +13,9 @@
 //   fp32  v_mfma_f32_16x16x4: the four K slots of MFMA t are the channels of
 //         tap t, the order of the generic kernel (the same sums bit for bit);
 //         every tap is one 4-byte read at a compile-time offset.
-// bf16 slots past the last tap meet zero weights and read the last tap's voxel,
-// so an infinity or NaN of the input reaches exactly the outputs whose window
-// holds it.
+// bf16 slots past the last tap read zeros (an LDS area that no tile writes; the
+// lanes that hold them leave out the row's offset), so an infinity or NaN of the
+// input reaches exactly the outputs whose window holds it, and as itself.
 //
 // Voxel order inside a tile: row r = 4 q + j is (h = j >> 1, w = 2 q + (j & 1))
 // and two tiles (dd = 0, 1) make the 2 x 2 x 8 voxels of four pooling windows;
@@ -23,8 +23,8 @@
 // (even and odd voxels) by lane writes, 16 lanes to each of the four (dd, hh)
 // rows, and two byte permutes put them into the mask tensor's order.
 //
-// Persistent workgroups (four per compute unit: 36 KB of LDS and at most 128
-// registers each) form the weight fragments once; tiles go to the XCDs in
+// Persistent workgroups (four per compute unit: 39.8 KB of LDS in bf16, 37.5 in
+// fp32, and at most 128 registers each) form the weight fragments once; tiles go to the XCDs in
 // contiguous runs.
 // Bound by vector issue (45 instructions per 32 voxels, and about 20 more for
 // staging) beside the MFMAs in bf16, by the matrix core in fp32.  256^3 batch 2
@@ -63,11 +63,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
   using G = C4Geom<DT>;
   constexpr bool BF = DT == DT_BF16;
   constexpr int TW = G::TW, RP = G::RP, VB = G::VB;
-  __shared__ __attribute__((aligned(16))) unsigned char halo[C4HD * C4HH * RP];
+  // bf16: zeros behind the halo, as far as a row's reads reach from their address
+  constexpr int HB = C4HD * C4HH * RP, ZB = BF ? (C4HH * RP + (TW - 8) * VB + VB + 15) / 16 * 16 : 0;
+  __shared__ __attribute__((aligned(16))) unsigned char halo[HB + ZB];
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int r = lane & 15, g = lane >> 4;
+
+#pragma unroll
+  for (int k = 0; k < ZB; k += 256 * 16)
+    if (k + 16 * tid < ZB) *reinterpret_cast<u32x4_t *>(halo + HB + k + 16 * tid) = u32x4_t{0u, 0u, 0u, 0u};
 
   // ---- tap slots of this lane: LDS offsets (from the tile row's first voxel) and weights
   const int voff = (((r & 3) >> 1) * RP) + (2 * (r >> 2) + (r & 1)) * VB;
@@ -79,12 +85,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
 #pragma unroll
     for (int m = 0; m < 4; ++m) {
       const int s = 4 * m + g;
-      int t0 = 2 * s, t1 = 2 * s + 1;
+      const int t0 = 2 * s, t1 = 2 * s + 1;
       const bool ok0 = t0 < 27, ok1 = t1 < 27;
-      t0 = ok0 ? t0 : 26;
-      t1 = ok1 ? t1 : 26;
-      a0[m] = voff + tap_off(t0);
-      a1[m] = voff + tap_off(t1);
+      a0[m] = ok0 ? voff + tap_off(t0) : HB;
+      a1[m] = ok1 ? voff + tap_off(t1) : HB;
       Vec16<DT_BF16> v;
 #pragma unroll
       for (int c = 0; c < 4; ++c) {
@@ -125,7 +129,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
       const int bd = ri / (C4TH / 2), bh = ri % (C4TH / 2);
       const int vd0 = od0 + 2 * bd, vh0 = oh0 + 2 * bh;
       if (vd0 >= p.od || vh0 >= p.oh) continue;
-      const unsigned char *hb = halo + (2 * bd * C4HH + 2 * bh) * RP;
+      const int rb = (2 * bd * C4HH + 2 * bh) * RP;  // the brick row's first halo row
+      int b0[4], b1[4];
+#pragma unroll
+      for (int m = 0; m < 4; ++m) {
+        b0[m] = BF ? a0[m] + (m < 3 || g < 2 ? rb : 0) : 0;
+        b1[m] = BF ? a1[m] + (m < 3 || g < 1 ? rb : 0) : 0;
+      }
       uint32_t me = 0, mo = 0;  // lane 16 (2 dd + hh) + 2 seg + half: ballots of even / odd voxels
       const int pd_ = vd0 >> 1, ph_ = vh0 >> 1;
       const bool prow_ok = pd_ < p.pod && ph_ < p.poh;
@@ -138,12 +148,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
 #pragma unroll
         for (int dd = 0; dd < 2; ++dd) {
           acc[dd] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-          const unsigned char *hs = hb + dd * C4HH * RP + 8 * sg * VB;
+          const unsigned char *hs = halo + dd * C4HH * RP + 8 * sg * VB;
           if constexpr (BF) {
 #pragma unroll
             for (int m = 0; m < 4; ++m) {
-              const u32x2_t lo = *reinterpret_cast<const u32x2_t *>(hs + a0[m]);
-              const u32x2_t hi = *reinterpret_cast<const u32x2_t *>(hs + a1[m]);
+              const u32x2_t lo = *reinterpret_cast<const u32x2_t *>(hs + b0[m]);
+              const u32x2_t hi = *reinterpret_cast<const u32x2_t *>(hs + b1[m]);
               u32x4_t av = {lo[0], lo[1], hi[0], hi[1]};
               if (FUSED && m == 3) av[2] = g == 1 ? 0x3f803f80u : av[2];  // the bias slots' ones
               acc[dd] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, av), bwb[m], acc[dd], 0, 0, 0);
@@ -152,7 +162,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
 #pragma unroll
             for (int t = 0; t < 27; ++t)
               acc[dd] = __builtin_amdgcn_mfma_f32_16x16x4f32(
-                  *reinterpret_cast<const float *>(hs + voff + 4 * g + tap_off(t)), bwf[t], acc[dd], 0, 0, 0);
+                  *reinterpret_cast<const float *>(hs + rb + voff + 4 * g + tap_off(t)), bwf[t], acc[dd], 0, 0, 0);
           }
         }
         // this lane: channel r, rows 4 g + j -> voxel (hh = j >> 1, w = 8 sg + 2 g + (j & 1))

@@ -215,3 +215,28 @@ def test_backward_weights_steep_slope(ci, dt, w):
     dw, db, rw, rb = gradient((1, (6, 8, w), "same", 4e6), ci, dt, keep=1.0)
     same_class(dw, rw, 5e-3 if dt == "bf16" else TOL["f32"])
     same_class(db, rb, 1e-5)
+
+
+@pytest.mark.parametrize("value", [np.inf, -np.inf])
+def test_forward_infinity_stays_one(value):
+    """Four channels, bf16: every output whose window holds an infinite voxel
+    is infinite (not NaN), at each of the 27 taps."""
+    desc = B.make_desc(1, (6, 9, 21), 4, 16, 3, 1, "same", "bf16")
+    rng = np.random.default_rng(36)
+    xs = rng.standard_normal((1, 6, 9, 21, 4))
+    xs[0, 2, 4, 7, 1] = value
+    x, w = dev(xs, "bf16"), dev(rng.standard_normal((3, 3, 3, 4, 16)), "bf16")
+    z = torch.full((1, 6, 9, 21, 16), float("nan"), dtype=torch.bfloat16, device="cuda")
+    B.cf_conv3d_fwd(desc, x, w, z)
+    b = torch.full((16,), 0.25, device="cuda")
+    out = torch.full((1, 3, 4, 10, 16), float("nan"), dtype=torch.bfloat16, device="cuda")
+    mask = torch.zeros(B.cf_conv3d_mask_bytes(desc), dtype=torch.uint8, device="cuda")
+    B.cf_conv3d_fwd_fused(desc, x, w, b, 0.2, B.CF_FUSE_POOL2, out, mask)
+    torch.cuda.synchronize()
+    ref = oracle.conv3d_fwd(to_np(x), to_np(w))
+    assert np.isinf(ref).sum() == 27 * 16
+    same_class(to_np(z), ref, TOL["bf16"])
+    with np.errstate(invalid="ignore"):
+        u = ref + 0.25
+        same_class(to_np(out), oracle.avgpool3d_fwd(np.where(u > 0, u, 0.2 * u)), TOL["bf16"])
+    assert np.array_equal(unpack(mask, u)[np.isinf(u)], (u > 0)[np.isinf(u)])
