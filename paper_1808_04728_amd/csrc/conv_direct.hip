@@ -941,6 +941,24 @@ long long count_tiles(const DirParams &p, int bm) {
   return tiles;
 }
 
+// k-steps one compute unit runs in a backward-data launch of row tiles of bm rows and
+// ny column blocks: whole rounds of workgroups where all tiles are alike; with
+// several stride classes the longest tile, or the average where that is more, with a
+// share of the longest tile for the end of the launch
+double tile_load(const DirParams &p, int bm, int ny) {
+  double sum = 0.0, longest = 0.0;
+  long long tiles = 0;
+  for (int c = 0; c < p.ncls; ++c) {
+    const long long t = (p.cls[c].m + bm - 1) / bm;
+    const double steps = (double)p.cls[c].ntap * (p.sc / 32);
+    if (t > 0) longest = std::max(longest, steps);
+    tiles += t * ny;
+    sum += (double)(t * ny) * steps;
+  }
+  if (p.ncls == 1) return (double)((tiles + kNumCUs - 1) / kNumCUs) * longest;
+  return sum <= kNumCUs * longest ? longest : sum / kNumCUs + 0.25 * longest;
+}
+
 // Tile choice (measured on the deep layers of the stack): the largest row
 // tile that still yields 256 workgroups (one per compute unit); more rows per
 // wave amortise the weight stream, waves along K keep every wave busy when
@@ -949,15 +967,22 @@ long long count_tiles(const DirParams &p, int bm) {
 // forward kernels (their per-step weight staging leaves load latency exposed
 // at these row counts), one for backward-data (bound by L2 -> L1 traffic,
 // where a deeper ring only adds registers) -- measured on the stack's layers.
-// Backward-data picks by cost instead: a tile's time relative to the 16-row one
-// (measured with one workgroup per compute unit: 11, 13, 16, 29 us plain, 13, 15,
-// 22, 29, 42 from (dy, y), on the 64 -> 64 layer) times the rounds of 256
-// workgroups its launch takes -- a second, nearly empty round costs a whole one
-// (13^3 batch 4 from (dy, y): 275 32-row tiles 28.8 us, 138 64-row tiles 23.7;
-// 256 -> 256 on 10^3 batch 3 33.2 -> 26.6, on 13^3 batch 4 90.0 -> 73.6).
+// Backward-data picks by cost instead: the k-steps that a compute unit runs one
+// after the other (tile_load) times what one k-step of the tile takes against the
+// 16-row tile's (slopes over one and more rounds on 64 -> 64, 64 -> 128, 128 -> 128
+// and 256 -> 256 layers: 0.17, 0.2, 0.36, 0.68 us for 16, 32, 64 and 128 rows; the
+// 64-row tile of two row waves never wins; the stride classes' short tiles favour 32
+// rows a little more).  With 32 output channels a k-step's rows
+// are 64 bytes and the two-row-wave tile is the better one of the 64-row tiles (128 ->
+// 32 on 29 x 35 x 40 from (dy, y): 37.6 us against 47.5 and, with 32 rows, 41.3; from a
+// pooled gradient two 32-row rounds beat it: 256 -> 32 on 11 x 16 x 16 9.6 and 12.0).  Both sides of
+// its steps, from (dy, y): 64 -> 64 on 20^3, 250 32-row tiles 15.7 us (64 rows 22.4),
+// 20 x 20 x 22, 275 tiles 27.9 (64 rows 22.5), 30 x 22 x 22 batch 2, 908 tiles 52.9
+// (128 rows 40.4); stride 2, 64 -> 64 3^3 on 20 x 19 x 14 batch 2, 32 rows 8.3 (16 rows
+// 9.0, 64 rows 10.6).
 // CF_DIRECT_TILE="fm,wm,wk" and CF_DIRECT_PF force a variant (tests cover
 // every one this way).
-DirCfg choose_cfg(DirParams &p, int fn, bool fwd, bool dyy = false) {
+DirCfg choose_cfg(DirParams &p, int fn, bool fwd, bool pooled = false) {
   static const DirCfg cand[] = {{4, 2, 2, 1}, {2, 2, 2, 1}, {4, 1, 4, 1}, {2, 1, 4, 1}, {1, 1, 4, 1}};
   int pf = 0;
   if (const char *e = getenv("CF_DIRECT_PF")) pf = atoi(e);
@@ -981,11 +1006,12 @@ DirCfg choose_cfg(DirParams &p, int fn, bool fwd, bool dyy = false) {
           break;
         }
     } else {
-      static const double plain[] = {2.6, 2.0, 1.47, 1.17, 1.0}, from_dyy[] = {3.2, 2.2, 1.7, 1.17, 1.0};
+      const double wide[] = {3.9, 2.65, 2.1, p.ncls == 1 ? 1.27 : 1.145, 1.0};
+      const double narrow[] = {5.1, 2.53, 2.9, pooled ? 1.25 : 1.41, 1.0};
       double best = 0.0;
       for (int i = 4; i >= 0; --i) {
-        const long long wgs = count_tiles(p, 16 * cand[i].fm * cand[i].wm) * ny;
-        const double cost = (double)((wgs + kNumCUs - 1) / kNumCUs) * (dyy ? from_dyy[i] : plain[i]);
+        const double cost =
+            tile_load(p, 16 * cand[i].fm * cand[i].wm, ny) * (p.sc > 32 ? wide[i] : narrow[i]);
         if (i == 4 || cost < best) {
           best = cost;
           pick = cand[i];
@@ -1019,19 +1045,26 @@ bool direct_supported(const ConvShape &s, bool fwd) {
 // LDS-staged kernel when its row tiles alone fill the machine (>= 256
 // workgroups), with 128-row tiles if they do, else 64-row tiles; 0 = the
 // register-streaming kernel.  CF_DIRECT_KERNEL=reg / lds128 / lds64 forces a
-// choice (tests cover every kernel on small shapes this way).  Backward-data
-// takes it from 128 workgroups of 64-row tiles on, and 128-row tiles from 512
-// (64 -> 64 on 13^3 batch 4, 138 tiles: 21.6 -> 13.9 us; 256 -> 256 on 10^3 batch 3,
-// 188: 25.1 -> 15.3; 4096 rows, 64 tiles: 13.7 against the register kernel's 11.2;
-// 64- against 128-row tiles: 18.1 and 20.3 us on 16^3 batch 8, 133 and 125 on the
-// 30^3 VALID layer with 1688 128-row tiles).
-int choose_lds(DirParams &p, int ny, bool fwd) {
+// choice (tests cover every kernel on small shapes this way).
+// Backward-data from a stored dz takes it once the register kernel's 32-row tiles
+// need a second round of workgroups (64 -> 64 on 20^3, 250 tiles: 12.1 us against
+// 13.0; 20 x 20 x 22, 275: 21.6 and, with 64 rows, 16.0 against 13.0; 256 -> 256 on 8^3,
+// 256: 13.5 against 14.5, 320: 24.5 against 14.6), with 128-row tiles from four
+// 64-row tiles per compute unit on (64 -> 64: 665 of them 20.9 and 23.1 us, 862 28.4
+// and 24.0; 256 -> 256: 384 17.9 and 21.1, 808 33.8 and 26.7).  From a pooled gradient
+// its fragments do twice the products behind one wait, and it needs two workgroups
+// per compute unit (64 -> 64: 216 64-row tiles 26.3 us against the register kernel's
+// 18.1, 253 26.4 against 18.1, 454 30.5 against 31.0; 128 -> 128 on 8^3 batch 8, 128
+// tiles: 16.8 against 9.3); its 64-row tiles are never the worse ones (128 -> 256, 1166
+// tiles: 65 us and 80; 256 -> 256, 3748: 169 and 182).
+int choose_lds(DirParams &p, int ny, bool fwd, bool pooled = false) {
   if (const char *e = getenv("CF_DIRECT_KERNEL")) {
     if (!strcmp(e, "reg")) return 0;
     if (!strcmp(e, "lds128")) return 2;
     if (!strcmp(e, "lds64")) return 1;
   }
-  if (!fwd) return count_tiles(p, 128) * ny >= 512 ? 2 : count_tiles(p, 64) * ny >= 128 ? 1 : 0;
+  if (pooled) return count_tiles(p, 64) * ny > kNumCUs ? 1 : 0;
+  if (!fwd) return count_tiles(p, 64) * ny > 3 * kNumCUs ? 2 : count_tiles(p, 32) * ny > kNumCUs ? 1 : 0;
   if ((long long)assign_tiles(p, 128) * ny >= 256) return 2;
   if ((long long)assign_tiles(p, 64) * ny >= 256) return 1;
   return 0;
@@ -1149,12 +1182,12 @@ hipError_t launch_conv_bwd_data_direct_fused(const ConvShape &s, const void *g, 
   }
   const int fn = p.dc % 64 == 0 ? 4 : 2;
   // pooled gradient: the LDS-staged kernel when its row tiles fill the machine
-  // (as the plain backward-data); the register kernel otherwise and for (dy, y)
+  // twice; the register kernel otherwise and for (dy, y)
   if (gm == GRAD_POOL)
-    if (const int fm = choose_lds(p, p.dc / (16 * fn), false))
+    if (const int fm = choose_lds(p, p.dc / (16 * fn), false, true))
       return fn == 4 ? launch_lds<false, 4, false, false, GRAD_POOL>(fm, p, g, w, nullptr, dx, nullptr, st, aux)
                      : launch_lds<false, 2, false, false, GRAD_POOL>(fm, p, g, w, nullptr, dx, nullptr, st, aux);
-  const DirCfg c = choose_cfg(p, fn, false, gm == GRAD_DYY);
+  const DirCfg c = choose_cfg(p, fn, false, gm == GRAD_POOL);
   const int tiles = assign_tiles(p, 16 * c.fm * c.wm);
   return gm == GRAD_POOL ? bwd_data_fused_t<GRAD_POOL>(c, p, tiles, fn, g, aux, w, dx, st)
                          : bwd_data_fused_t<GRAD_DYY>(c, p, tiles, fn, g, aux, w, dx, st);

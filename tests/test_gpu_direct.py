@@ -303,3 +303,70 @@ def test_direct_wgrad_matches_generic(case, monkeypatch):
         out.append(to_np(dw))
     scale = np.abs(out[1]).max()
     assert np.abs(out[0] - out[1]).max() <= 1e-5 * scale
+
+
+# backward-data on both sides of its dispatch's steps: form, N, (D, H, W), CI, CO, k, s and what it should run
+STEPS = [
+    ("dz", 1, (16, 16, 16), 64, 64, 2, 1, "1,1,4"),    # 256 16-row tiles: one round
+    ("dz", 1, (16, 16, 17), 64, 64, 2, 1, "2,1,4"),
+    ("dz", 1, (16, 16, 32), 64, 64, 2, 1, "2,1,4"),    # 256 32-row tiles
+    ("dz", 1, (16, 16, 33), 64, 64, 2, 1, "lds64"),
+    ("dz", 1, (32, 32, 48), 64, 64, 1, 1, "lds64"),    # 768 64-row tiles: three a compute unit
+    ("dz", 1, (32, 32, 49), 64, 64, 1, 1, "lds128"),
+    ("dz", 2, (12, 13, 12), 128, 64, 2, 1, "2,1,4"),   # two column blocks
+    ("dy", 1, (16, 16, 33), 64, 64, 2, 1, "4,1,4"),
+    ("dy", 1, (16, 32, 33), 64, 64, 2, 1, "2,1,4"),    # three 32-row rounds against two of 64 and one of 128
+    ("dy", 1, (32, 32, 25), 64, 64, 2, 1, "4,2,2"),
+    ("dy", 2, (20, 19, 14), 64, 64, 3, 2, "2,1,4"),    # stride classes of 1 to 8 taps
+    ("dy", 1, (11, 16, 16), 64, 32, 2, 1, "1,1,4"),
+    ("dy", 1, (32, 32, 25), 64, 32, 2, 1, "2,2,2"),    # 32 output channels
+    ("pool", 1, (16, 32, 32), 64, 64, 2, 1, "4,1,4"),  # 256 64-row tiles
+    ("pool", 1, (16, 32, 34), 64, 64, 2, 1, "lds64"),
+    ("pool", 1, (24, 24, 16), 32, 64, 4, 2, "2,1,4"),
+]
+
+
+@pytest.mark.parametrize("case", STEPS, ids=lambda c: "%s_n%d_%dx%dx%d_c%d-%d_k%d_s%d_%s" % (c[0], c[1], *c[2], *c[3:]))
+def test_backward_data_dispatch(case, monkeypatch):
+    form, N, dhw, CI, CO, k, s, kern = case
+    desc = B.make_desc(N, dhw, CI, CO, k, s, "same", "bf16")
+    od = B.cf_conv3d_out_shape(desc)
+    rng = np.random.default_rng(40)
+    w = dev(rng.standard_normal((k, k, k, CI, CO)) / np.sqrt(k ** 3 * CO), "bf16")
+    gshape = tuple(t // 2 for t in od) if form == "pool" else od
+    g = dev(rng.standard_normal((N, *gshape, CO)), "bf16")
+    y = dev(rng.standard_normal((N, *od, CO)), "bf16")
+    mask = torch.as_tensor(rng.integers(0, 256, B.cf_conv3d_mask_bytes(desc), dtype=np.uint8), device="cuda")
+
+    def run():
+        dx = torch.full((N, *dhw, CI), float("nan"), dtype=torch.bfloat16, device="cuda")
+        if form == "dz":
+            B.cf_conv3d_bwd_data(desc, g, w, dx)
+        elif form == "dy":
+            B.cf_conv3d_bwd_data_fused(desc, g, y, w, 0.2, 0, dx)
+        else:
+            B.cf_conv3d_bwd_data_fused(desc, g, mask, w, 0.2, B.CF_FUSE_POOL2, dx)
+        torch.cuda.synchronize()
+        return dx
+
+    dx = run()
+    if kern.startswith("lds"):
+        monkeypatch.setenv("CF_DIRECT_KERNEL", kern)
+    else:
+        monkeypatch.setenv("CF_DIRECT_KERNEL", "reg")
+        monkeypatch.setenv("CF_DIRECT_TILE", kern)
+    same = torch.equal(dx, run())
+    assert same
+    if form == "dz":
+        dz = to_np(g)
+    elif form == "dy":
+        dz, _ = oracle.bias_lrelu_bwd(to_np(g), to_np(y), 0.2)
+    else:
+        bits = unpack_mask(mask, N * od[0] * od[1] * od[2] * CO).reshape(N, *od, CO)
+        dz = oracle.avgpool3d_bwd(to_np(g), od) * np.where(bits, 1.0, 0.2)
+    got = to_np(dx)
+    assert np.isfinite(got).all()
+    idx = np.stack([rng.integers(0, t, 600) for t in (N, *dhw, CI)], 1)
+    idx[:200, :4] = np.array([N, *dhw]) - 1 - rng.integers(0, 2, (200, 1)) * (np.array([N, *dhw]) > 1)
+    ref = oracle.conv3d_bwd_data_points(dz, to_np(w), dhw, idx, stride=s)
+    assert maxabs_err(got[tuple(idx.T)], ref) <= TOL["bf16"]
