@@ -931,7 +931,10 @@ int f_pick(const ConvShape &s, FParams &p, double *cost, bool fwd, bool dyy) {
   const bool os = !fwd && !dyy && FN == 1 && f_os_ok(s, p);
   const bool four = fwd && f_tk() ? f_tk_ok(s, p) : os || f_shift_ok(s, p);
   // a destination w row per tile (48 rows of MFMAs): from five tiles per compute
-  // unit on it beats the linear tiles (37^3, 1369 rows: 74.7 -> 58.4 us)
+  // unit on it beats the linear tiles wherever it was tried (37^3, 1369 rows: 74.7 ->
+  // 58.4 us; 31 x 42 x 48, 1302 rows: 87.2 -> 57.3; 35 x 40 x 33, 1400 rows: 57.2 ->
+  // 56.7).  Below that the widest rows win too (30 x 32 x 48, 960 rows: 57.5 -> 38.9)
+  // and the narrowest tie (30 x 40 x 33, 1200 rows: 56.9 and 56.3)
   const int jw = (int)p.cls[0].fw.div;
   const bool rowtiles = os && jw > 32 && jw <= 48 && p.cls[0].m / jw >= 5 * kNumCUs;
   if (four && !getenv("CF_F32_TILE") &&
@@ -1017,7 +1020,9 @@ int f_pick_fn(const ConvShape &s, FParams &p, int fnmax, bool fwd, bool dyy = fa
     const int pick = f == 4   ? f_pick<4>(s, p, &c, fwd, dyy)
                      : f == 2 ? f_pick<2>(s, p, &c, fwd, dyy)
                               : f_pick<1>(s, p, &c, fwd, dyy);
-    if (pick < 0) return fnmax;  // shift mode: the large layers keep the widest groups
+    // a four-tap mode, at the widest group or a narrower one: a layer of that size has
+    // workgroups enough at any width and keeps the widest
+    if (pick < 0) return fnmax;
     if (f == fnmax || c < best) {
       best = c;
       best_fn = f;

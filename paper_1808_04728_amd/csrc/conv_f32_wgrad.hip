@@ -427,7 +427,8 @@ L1F32Params l1_params(const ConvShape &s, float alpha) {
 bool l1f32_wgrad_supported(const ConvShape &s) {
   const long long xin = (long long)s.n * s.d * s.h * s.w, vout = (long long)s.n * s.od * s.oh * s.ow;
   return s.dtype == DT_F32 && s.ci == 1 && s.co == 16 && s.sd == 1 && s.sh == 1 && s.sw == 1 && s.kd == s.kh &&
-         s.kd == s.kw && (s.kd == 2 || s.kd == 3) && s.pw <= 1 && s.kd - s.pw <= 3 && s.od >= 2 && s.oh >= 2 && xin * 4 < (1LL << 31) && vout * 64 < (1LL << 31);
+         s.kd == s.kw && (s.kd == 2 || s.kd == 3) && s.pw <= 1 && s.kd - s.pw <= 3 && s.od >= 2 && s.oh >= 2 &&
+         xin * 4 < (1LL << 31) && vout * 64 < (1LL << 31);
 }
 
 size_t l1f32_wgrad_workspace(const ConvShape &s) {

@@ -227,7 +227,8 @@ hipError_t launch_c4(const ConvShape &s, const void *x, const void *w, const flo
 
 }  // namespace
 
-// four input channels, 3^3, 16 outputs, stride 1; a tile count and halo offsets below 2^31
+// four input channels, 3^3, 16 outputs, stride 1; a tile count and halo offsets below
+// 2^31 (inputs of more than 44 M voxels in an h w slice stay with the general kernels)
 bool l1c4_supported(const ConvShape &s) {
   long long total;
   c4_tiles(s, 32, &total);

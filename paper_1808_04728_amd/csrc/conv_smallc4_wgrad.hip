@@ -39,6 +39,7 @@
 #include "cf_common.h"
 #include "cf_kernels.h"
 #include "conv_smallc4_halo.h"
+#include "row_load.h"
 
 #include <algorithm>
 
@@ -53,7 +54,6 @@ constexpr int M = 108;                     // (tap, ci) rows
 typedef short v4i16_t __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) v4i16_t lds_v4i16_t;
 typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
-typedef uint32_t u32x4a2_t __attribute__((ext_vector_type(4), aligned(2)));
 
 __device__ __forceinline__ u32x2_t tr4(const unsigned char *p) {
   return __builtin_bit_cast(u32x2_t, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16_t *)p));
@@ -110,15 +110,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
       const int row = tid >> 2;
       const int vd = od0 + row / TH, vh = oh0 + row % TH, vw = ow0 + 8 * (tid & 3);
       if (vd < p.od && vh < p.oh && vw < p.ow) {
-        const uint16_t *mrow = mask16 + (((long long)n * p.od + vd) * p.oh + vh) * p.ow + vw;
-        if (vw + 8 <= p.ow) {
-          mv = *reinterpret_cast<const u32x4a2_t *>(mrow);
-        } else {
-          uint32_t h[8];
-#pragma unroll
-          for (int u = 0; u < 8; ++u) h[u] = vw + u < p.ow ? mrow[u] : 0u;
-          mv = u32x4_t{h[0] | h[1] << 16, h[2] | h[3] << 16, h[4] | h[5] << 16, h[6] | h[7] << 16};
-        }
+        mv = load_mask8(mask16 + (((long long)n * p.od + vd) * p.oh + vh) * p.ow + vw, vw, p.ow);
       }
     }
   };

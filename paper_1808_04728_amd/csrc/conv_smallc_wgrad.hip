@@ -466,17 +466,7 @@ __global__ __launch_bounds__(256) void l1_wgrad_kernel(const uint16_t *__restric
       const int vd = od0 + row / TH, vh = oh0 + row % TH, vw = ow0 + 8 * (tid & 3);
       if (vd < p.od && vh < p.oh && vw < p.ow) {
         const uint16_t *mrow = mask16 + (int)__umul24(__umul24(n * p.od + vd, p.oh) + vh, p.ow);
-        if (vw + 8 <= p.ow) {
-          mv = *reinterpret_cast<const u32x4a2_t *>(mrow + vw);
-        } else {
-          // ragged end of a row: the voxels past it pool into no pooled voxel
-          // (their B values are zero), so their bits may be anything; read only
-          // the row's own voxels (the last row ends at the end of the buffer)
-          uint32_t h[8];
-#pragma unroll
-          for (int u = 0; u < 8; ++u) h[u] = vw + u < p.ow ? mrow[vw + u] : 0u;
-          mv = u32x4_t{h[0] | h[1] << 16, h[2] | h[3] << 16, h[4] | h[5] << 16, h[6] | h[7] << 16};
-        }
+        mv = load_mask8(mrow + vw, vw, p.ow);
       }
     }
   };
@@ -775,15 +765,15 @@ hipError_t launch_smallc_wgrad_dz(const ConvShape &s, const void *x, const void 
   const SmallcParams p = params(s, w);
   float *pw = (float *)ws;
   const bool aln = s.w % 8 == 0;
+  auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(w.blocks), dim3(256), 0, st, (const uint16_t *)x, (const uint16_t *)dz, pw, p);
+  };
   if (s.kd == 2)
-    hipLaunchKernelGGL((aln ? l1_wgrad_dz_kernel<2, 0, true> : l1_wgrad_dz_kernel<2, 0, false>), dim3(w.blocks), dim3(256), 0, st, (const uint16_t *)x,
-                       (const uint16_t *)dz, pw, p);
+    aln ? launch(l1_wgrad_dz_kernel<2, 0, true>) : launch(l1_wgrad_dz_kernel<2, 0, false>);
   else if (s.pw == 0)
-    hipLaunchKernelGGL((aln ? l1_wgrad_dz_kernel<3, 0, true> : l1_wgrad_dz_kernel<3, 0, false>), dim3(w.blocks), dim3(256), 0, st, (const uint16_t *)x,
-                       (const uint16_t *)dz, pw, p);
+    aln ? launch(l1_wgrad_dz_kernel<3, 0, true>) : launch(l1_wgrad_dz_kernel<3, 0, false>);
   else
-    hipLaunchKernelGGL((aln ? l1_wgrad_dz_kernel<3, 1, true> : l1_wgrad_dz_kernel<3, 1, false>), dim3(w.blocks), dim3(256), 0, st, (const uint16_t *)x,
-                       (const uint16_t *)dz, pw, p);
+    aln ? launch(l1_wgrad_dz_kernel<3, 1, true>) : launch(l1_wgrad_dz_kernel<3, 1, false>);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   return launch_sum_rows(pw, dw, w.blocks, s.kd * s.kh * s.kw * s.co, st);
@@ -817,15 +807,16 @@ hipError_t launch_smallc_wgrad_fused(const ConvShape &s, const void *x, const vo
     float *pw = (float *)ws;
     float *pb = pw + (size_t)w.blocks * M * s.co;
     const bool aln = s.w % 8 == 0;
+    auto launch = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, dim3(w.blocks), dim3(256), 0, st, (const uint16_t *)x, (const uint16_t *)dp, mask, alpha,
+                         pw, pb, p);
+    };
     if (s.kd == 2)
-      hipLaunchKernelGGL((aln ? l1_wgrad_kernel<2, 0, true> : l1_wgrad_kernel<2, 0, false>), dim3(w.blocks), dim3(256), 0, st, (const uint16_t *)x,
-                         (const uint16_t *)dp, mask, alpha, pw, pb, p);
+      aln ? launch(l1_wgrad_kernel<2, 0, true>) : launch(l1_wgrad_kernel<2, 0, false>);
     else if (s.pw == 0)
-      hipLaunchKernelGGL((aln ? l1_wgrad_kernel<3, 0, true> : l1_wgrad_kernel<3, 0, false>), dim3(w.blocks), dim3(256), 0, st, (const uint16_t *)x,
-                         (const uint16_t *)dp, mask, alpha, pw, pb, p);
+      aln ? launch(l1_wgrad_kernel<3, 0, true>) : launch(l1_wgrad_kernel<3, 0, false>);
     else
-      hipLaunchKernelGGL((aln ? l1_wgrad_kernel<3, 1, true> : l1_wgrad_kernel<3, 1, false>), dim3(w.blocks), dim3(256), 0, st, (const uint16_t *)x,
-                         (const uint16_t *)dp, mask, alpha, pw, pb, p);
+      aln ? launch(l1_wgrad_kernel<3, 1, true>) : launch(l1_wgrad_kernel<3, 1, false>);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     e = launch_sum_rows(pw, dw, w.blocks, M * s.co, st);

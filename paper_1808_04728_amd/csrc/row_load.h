@@ -1,5 +1,6 @@
-// row_load.h -- eight consecutive bf16 voxels of a one-channel row that need
-// not start on any alignment, zero outside the row (gfx950).
+// row_load.h -- eight consecutive 16-bit elements of a row that need not start
+// on any alignment, zero outside the row (gfx950): bf16 voxels of a one-channel
+// input, 16-channel slope mask words.
 #pragma once
 
 #include "cf_common.h"
@@ -28,6 +29,17 @@ __device__ __forceinline__ u32x4_t load_run8(const uint16_t *xr, int c0, int w) 
     lo = s < 64 ? lo << s : 0;
   }
   return u32x4_t{(uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32)};
+}
+
+// the mask words of voxels c0 .. c0 + 7 (from m on) of a row of w > c0 voxels.  Past
+// its end only the row's own words are read (the last row ends at the end of the
+// buffer); those voxels pool into no window, so their bits may be anything.
+__device__ __forceinline__ u32x4_t load_mask8(const uint16_t *m, int c0, int w) {
+  if (c0 + 8 <= w) return *reinterpret_cast<const u32x4a2_t *>(m);
+  uint32_t h[8];
+#pragma unroll
+  for (int u = 0; u < 8; ++u) h[u] = c0 + u < w ? m[u] : 0u;
+  return u32x4_t{h[0] | h[1] << 16, h[2] | h[3] << 16, h[4] | h[5] << 16, h[6] | h[7] << 16};
 }
 
 }  // namespace cf
