@@ -165,11 +165,14 @@ def gradient(case, ci, dt, spoil_x=(), spoil_g=(), keep=0.5):
     mb = np.zeros(B.cf_conv3d_mask_bytes(desc), np.uint8)
     packed = np.packbits(bits.reshape(-1), bitorder="little")
     mb[:packed.size] = packed
-    dw = torch.full((3, 3, 3, ci, 16), float("nan"), device="cuda")
-    db = torch.full((16,), float("nan"), device="cuda")
-    ws = torch.empty(max(16, B.cf_conv3d_bwd_weight_fused_workspace_size(desc)), dtype=torch.uint8, device="cuda")
+    nws = max(16, B.cf_conv3d_bwd_weight_fused_workspace_size(desc))
+    # 64 guard bytes on both sides of every output and of the workspace
+    bufs = [torch.full((n + 128,), 0xA5, dtype=torch.uint8, device="cuda") for n in (27 * ci * 64, 64, nws)]
+    dw, db, ws = bufs[0][64:-64].view(torch.float32).view(3, 3, 3, ci, 16), bufs[1][64:-64].view(torch.float32), bufs[2][64:-64]
     B.cf_conv3d_bwd_weight_fused(desc, x, g, torch.as_tensor(mb, device="cuda"), alpha, B.CF_FUSE_POOL2, dw, db, ws)
     torch.cuda.synchronize()
+    for t in bufs:
+        assert bool((t[:64] == 0xA5).all()) and bool((t[-64:] == 0xA5).all())
     with np.errstate(invalid="ignore"):
         dz = oracle.avgpool3d_bwd(to_np(g), od) * np.where(bits.astype(bool), 1.0, alpha)
         return to_np(dw), to_np(db), oracle.conv3d_bwd_weight(to_np(x), dz, 3, pad=pad), dz.sum(axis=(0, 1, 2, 3))
@@ -240,3 +243,28 @@ def test_forward_infinity_stays_one(value):
         u = ref + 0.25
         same_class(to_np(out), oracle.avgpool3d_fwd(np.where(u > 0, u, 0.2 * u)), TOL["bf16"])
     assert np.array_equal(unpack(mask, u)[np.isinf(u)], (u > 0)[np.isinf(u)])
+
+
+# rows shorter than a 16-byte vector of bf16, the smallest depths and heights, odd output widths
+NARROW = [
+    (1, (2, 3, 3), "same", 0.01),
+    (2, (3, 2, 5), "same", 0.2),
+    (1, (4, 5, 5), "valid", 0.01),   # out (2, 3, 3)
+    (3, (5, 4, 7), "valid", 0.01),   # out (3, 2, 5)
+    (1, (3, 3, 7), "same", 1.5),
+    (2, (5, 7, 4), "valid", 0.01),   # out (3, 5, 2)
+    (1, (3, 9, 9), "same", 0.01),    # one voxel more than a vector
+]
+
+
+@pytest.mark.parametrize("ci,dt", [(1, "bf16"), (4, "bf16"), (1, "f32")])
+@pytest.mark.parametrize("case", NARROW, ids=name)
+def test_narrow_rows(case, ci, dt):
+    out, mask, z, b, alpha = forward(case, ci, dt)
+    u = z + b
+    assert maxabs_err(to_np(out), oracle.avgpool3d_fwd(oracle.bias_lrelu_fwd(z, b, alpha))) <= TOL[dt]
+    decided = np.abs(u) > 1e-5 * np.abs(u).max()
+    assert np.array_equal(unpack(mask, u)[decided], (u > 0)[decided])
+    dw, db, rw, rb = gradient(case, ci, dt)
+    same_class(dw, rw, 5e-3 if dt == "bf16" else TOL["f32"])
+    same_class(db, rb, 1e-5)
