@@ -30,13 +30,16 @@ def _t(dtype):
     return torch.bfloat16 if dtype == "bf16" else torch.float32
 
 
-#: bf16 stacks below this many FLOPs a step run their backward on one stream: the
-#: events and waits of a second one take the host about 25 us a layer, which only a
-#: step of 0.4 ms and more hides (six layers, one stream / two: 64^3 batch 4 199 / 236
-#: us, 96^3 batch 2 238 / 275, 128^3 batch 2 (113 GFLOP) 287 / 286, 96^3 batch 8 (190)
-#: 417 / 410, 128^3 batch 8 (475) 687 / 680; a single 64 -> 64 layer on 13^3 batch 4
-#: 65 / 73, the 32 -> 64 VALID layer on 30^3 batch 8 (124) 315 / 327; 120^3 batch 3 (147)
-#: 349 / 341, so the line lies between that layer on 31^3 (138) and this step)
+#: bf16 stacks below this many FLOPs a step run their backward on one stream.  The
+#: events and waits of a second one take the host about 25 us a layer, and its queue
+#: gains a step of six layers 1 to 2% at most (one stream / two, us: 64^3 batch 2 175 /
+#: 244, 100^3 batch 1 210 / 244, 128^3 batch 1 (59 GFLOP) 223 / 246, 128^3 batch 2 (119)
+#: 277 / 285, 112^3 batch 3 (119) 310 / 309, 120^3 batch 3 (146) 325 / 322, 96^3 batch
+#: 8 (200) 407 / 399, 144^3 batch 4 (338) 637 / 632, 128^3 batch 8 (475) 687 / 680).
+#: FLOPs stand for the device time that hides the host's; between 0.12 and 0.2
+#: TFLOP both ways are within 2%.  Single layers differ more either way: the 32 -> 64
+#: VALID layer on 31^3 batch 8 (138) 335 / 343 and on 32^3 (153) 375 / 391, 64 -> 64 on
+#: 13^3 batch 4 65 / 73, on 32^3 batch 8 (174) 667 / 628.
 OVERLAP_FLOPS = 1.4e11
 
 
