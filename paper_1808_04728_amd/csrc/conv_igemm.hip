@@ -570,17 +570,31 @@ hipError_t dispatch_wgrad(const WgradPlan &pl, const WgradParams &p, const void 
 
 }  // namespace
 
-// CF_CONV_KERNEL=igemm keeps forward and backward-data on the generic kernel
-// (tests compare it with the specialised fp32 kernel this way)
-static bool igemm_forced() {
+// CF_CONV_KERNEL=igemm keeps forward and backward-data on the generic kernel,
+// CF_CONV_KERNEL=c4 the fp32 four-channel forward on its own (tests compare the
+// specialised fp32 kernels with the generic one this way)
+static bool kernel_forced(const char *name) {
   const char *e = getenv("CF_CONV_KERNEL");
-  return e && !strcmp(e, "igemm");
+  return e && !strcmp(e, name);
+}
+
+static bool igemm_forced() { return kernel_forced("igemm"); }
+
+// Four input channels in fp32 (the same bits from both kernels): a wave of the
+// halo kernel goes through its 4 x 8 x 32 tile alone, 2.3 us for every eight voxels of
+// a row, while the generic kernel takes 10 us up to 2^15 voxels (one round of its
+// workgroups) and 13 us and more from there on.  So rows of up to 16 voxels run the
+// halo kernel at any size (16^3 9.9 -> 8.0 us), longer ones past 2^15 voxels (32^3:
+// 10.3 us generic, 12.9 halo; 32 x 32 x 36 13.2 and 13.0; 32 x 32 x 91 18.0 and 13.5).
+static bool l1c4_fwd_taken(const ConvShape &s) {
+  if (!l1c4_supported(s) || igemm_forced()) return false;
+  return s.dtype == DT_BF16 || s.ow <= 16 || (long long)s.n * s.od * s.oh * s.ow > (1 << 15) || kernel_forced("c4");
 }
 
 hipError_t launch_conv_fwd(const ConvShape &s, const void *x, const void *w, void *z,
                            hipStream_t st) {
   // four input channels: operand fragments of whole voxels
-  if (l1c4_supported(s) && !igemm_forced()) return launch_conv_fwd_l1c4(s, x, w, nullptr, 0.f, z, nullptr, false, st);
+  if (l1c4_fwd_taken(s)) return launch_conv_fwd_l1c4(s, x, w, nullptr, 0.f, z, nullptr, false, st);
   // few input channels: the direct halo kernel (one im2col gather per MFMA tile)
   if (smallc_supported(s, false))
     return launch_conv_fwd_smallc(s, x, w, nullptr, 0.f, z, nullptr, false, st);

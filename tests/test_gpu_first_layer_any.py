@@ -268,3 +268,24 @@ def test_narrow_rows(case, ci, dt):
     dw, db, rw, rb = gradient(case, ci, dt)
     same_class(dw, rw, 5e-3 if dt == "bf16" else TOL["f32"])
     same_class(db, rb, 1e-5)
+
+
+# both sides of the fp32 four-channel forward's rule (rows of 16 voxels, 2^15 voxels) and the halo kernel below it
+@pytest.mark.parametrize("n,dhw,pad", [(1, (6, 9, 16), "same"), (1, (6, 9, 17), "same"), (1, (16, 32, 64), "same"),
+                                       (1, (16, 32, 65), "same"), (2, (7, 19, 69), "valid"), (2, (3, 5, 33), "same")])
+def test_four_channel_fp32_forward_rule(n, dhw, pad, monkeypatch):
+    """The plain fp32 forward by its rule, by the generic and by the halo
+    kernel: the same bits."""
+    desc = B.make_desc(n, dhw, 4, 16, 3, 1, pad, "f32")
+    rng = np.random.default_rng(37)
+    x = dev(rng.standard_normal((n, *dhw, 4)), "f32")
+    w = dev(rng.standard_normal((3, 3, 3, 4, 16)), "f32")
+    od = B.cf_conv3d_out_shape(desc)
+    z = [torch.full((n, *od, 16), float("nan"), device="cuda") for _ in range(3)]
+    B.cf_conv3d_fwd(desc, x, w, z[0])
+    for k, t in zip(("igemm", "c4"), z[1:]):
+        monkeypatch.setenv("CF_CONV_KERNEL", k)
+        B.cf_conv3d_fwd(desc, x, w, t)
+    torch.cuda.synchronize()
+    assert torch.equal(z[0], z[1]) and torch.equal(z[0], z[2])
+    assert maxabs_err(to_np(z[0]), oracle.conv3d_fwd(to_np(x), to_np(w), pad=pad)) <= TOL["f32"]
