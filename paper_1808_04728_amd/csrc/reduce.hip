@@ -21,11 +21,15 @@ namespace {
 
 constexpr int MAX_JOBS = 16;
 // Loads in flight per thread: a phase's rows are a serial chain of load rounds.
-// Sixteen for narrow matrices; eight for wide ones in batches of up to 40 MB (the
-// 64^3 fp32 step's sums 10.2 -> 8.1 us, 33 MB of 45^3 partials 8.4 -> 7.3, a first
-// layer's alone 8.0 -> 5.6) and four beyond, where the machine is full anyway
-// (50 MB: 11.9 us with four, 12.5 with eight; 110 MB: 26.2 and 27.4).
-constexpr int FL_NARROW = 16, FL_WIDE = 8, FL_BIG = 4;
+// Sixteen for narrow matrices of more than twelve rows a phase; eight for wide ones in
+// batches of up to 40 MB (the 64^3 fp32 step's sums 10.2 -> 8.1 us, 33 MB of 45^3
+// partials 8.4 -> 7.3, a first layer's alone 8.0 -> 5.6) and four beyond, where the
+// machine is full anyway (50 MB: 11.9 us with four, 12.5 with eight; 110 MB: 26.2 and
+// 27.4).  A phase of a few rows wants no more in flight than it has: a round of
+// sixteen costs its sixteen loads whatever it adds up (136 x 32 3.57 us with it, 3.26
+// with four; 12 x 16 2.98 and 2.77; 900 x 16, 15 rows a phase, 3.48 and 3.74).
+constexpr int FL_NARROW = 16, FL_WIDE = 8, FL_FEW = 4;
+constexpr int kFewRows = 12;               // rows a phase
 constexpr long long kBigSum = 10LL << 20;  // elements
 
 struct RedJob {
@@ -84,13 +88,16 @@ __global__ __launch_bounds__(256) void sum_batch_kernel(const RedBatch b) {
     const int cols4 = J.cols >> 2;
     const float4 *part = reinterpret_cast<const float4 *>(J.part);
     if (c < cols4) {
-      if (b.big) s = sum_phase<FL_BIG>(part + c, cols4, ph, PH, rows, s);
+      if (b.big) s = sum_phase<FL_FEW>(part + c, cols4, ph, PH, rows, s);
       else s = sum_phase<FL_WIDE>(part + c, cols4, ph, PH, rows, s);
     }
   } else {
     const int cols = J.cols;
     const float *part = J.part;
-    if (c < cols) s.x = sum_phase<FL_NARROW>(part + c, cols, ph, PH, rows, s.x);
+    if (c < cols) {
+      if (b.big || rows <= kFewRows * PH) s.x = sum_phase<FL_FEW>(part + c, cols, ph, PH, rows, s.x);
+      else s.x = sum_phase<FL_NARROW>(part + c, cols, ph, PH, rows, s.x);
+    }
   }
   red[tid] = s;
   __syncthreads();

@@ -111,3 +111,39 @@ def test_reduce_partials_batch_matches_single_jobs():
         assert torch.equal(o, ref)
         want = p.double().sum(0).cpu().numpy() if r else np.zeros(c)
         assert np.allclose(o.cpu().numpy(), want, rtol=1e-5, atol=1e-5 * max(1, r))
+
+
+def _sum_as_documented(a):
+    """Column sums in the fixed order: phases of every ph-th row, each from its
+    first row on, then halves of the phases added up."""
+    rows, cols = a.shape
+    per, ph = (4 if cols < 256 else 64), 1
+    while ph < 64 and ph * per < rows:
+        ph *= 2
+    s = np.zeros((ph, cols), np.float32)
+    for r in range(0, rows, ph):
+        k = min(ph, rows - r)
+        s[:k] += a[r:r + k]
+    while ph > 1:
+        ph //= 2
+        s = s[:ph] + s[ph:2 * ph]
+    return s[0]
+
+
+# rows on both sides of a round of loads (4, 8, 16 a phase) and of the rule for few rows (12 a phase of 64)
+@pytest.mark.parametrize("big", [False, True])
+@pytest.mark.parametrize("cols", [16, 255, 257, 432])
+def test_sum_order_at_load_rounds(cols, big):
+    rng = np.random.default_rng(50)
+    rows = [1, 3, 5, 255, 257, 767, 768, 769, 1024, 1025]
+    parts = [rng.standard_normal((r, cols)).astype(np.float32) for r in rows]
+    if big:  # one more job takes the batch past 40 MB
+        parts.append(rng.standard_normal((20, 1 << 19)).astype(np.float32))
+    dparts = [torch.as_tensor(p, device="cuda") for p in parts]
+    outs = [torch.full((p.shape[1] + 8,), float("nan"), device="cuda") for p in parts]
+    B.cf_reduce_partials([B.cf_reduction(p.data_ptr(), o.data_ptr(), *p.shape) for p, o in zip(dparts, outs)])
+    torch.cuda.synchronize()
+    for p, o in zip(parts, outs):
+        got = o.cpu().numpy()
+        assert np.isnan(got[-8:]).all()
+        assert np.array_equal(got[:-8], _sum_as_documented(p))
