@@ -545,7 +545,8 @@ __device__ __forceinline__ f32x4_t head_tile(const float *A, int lda, int m, con
 // 2.5, forward 4.5, loss 2, backward 4.4 us, for under a microsecond of matrix
 // work); barriers that do not wait for the stores did not move it, nor did
 // touching the arguments' cache lines first.
-template <int DT>
+// OWN: the threads that load layer 1's weights (head_own).
+template <int DT, int OWN>
 __global__ __launch_bounds__(1024) void fc_head_tail_kernel(const HeadParams p) {
   using T = typename Store<DT>::T;
   __shared__ float wl[HEAD_WT];               // layer i >= 1: [K][N + 1]
@@ -560,7 +561,7 @@ __global__ __launch_bounds__(1024) void fc_head_tail_kernel(const HeadParams p) 
 
   // Everything the workgroup reads from global memory: layer 0's y and the
   // target (kept in zb[1] until the loss) requested first, then layer 1's weights
-  // by twelve waves and the other layers' and the biases by four.
+  // by twelve waves and the other layers' and the biases by four, or all by all.
   const int ny = m * p.dims[1], nt = m * p.dims[L];
   const T y0 = tid < ny ? ((const T *)p.y[0])[tid] : from_f32<DT>(0.f);
   const float tg = tid < nt ? p.target[tid] : 0.f;
@@ -570,8 +571,8 @@ __global__ __launch_bounds__(1024) void fc_head_tail_kernel(const HeadParams p) 
     for (int i = 1; i < L; ++i) {
       const int K = p.dims[i], N = p.dims[i + 1], KN = K * N;
       const T *w = (const T *)p.w[i];
-      const int t0 = i == 1 ? tid : tid - 768, ts = i == 1 ? 768 : 256;
-      const bool mine = i == 1 ? tid < 768 : tid >= 768;
+      const int t0 = OWN == 1024 || i == 1 ? tid : tid - OWN, ts = OWN == 1024 || i == 1 ? OWN : 1024 - OWN;
+      const bool mine = OWN == 1024 || (i == 1 ? tid < OWN : tid >= OWN);
       if (mine && N % EV == 0) {  // a vector lies in one row
         // 128 x 64 in one round of loads, two (bf16) or three (fp32) a thread: the whole
         // fp32 head at 6656 features, batch 1, 25.9 -> 25.4 us against a loop of two
@@ -873,6 +874,17 @@ bool fc_head_supported(int M, int L, const int *dims, int dtype) {
 
 size_t fc_head_workspace(int M, int L, const int *dims) { return fc_fwd_workspace(M, dims[0], dims[1]); }
 
+// Twelve of the tail's sixteen waves load layer 1's weights and four the rest, side by
+// side, while the rest is one round of their loads (128 -> 64 -> 3); more of it would
+// keep the four busy alone, so all load layer after layer (batch 1, fp32, 4096 -> 64 ->
+// 96 -> 96 -> 1: 29.8 us with the four, 29.0 with all; 1176 -> 64 -> 100 -> 64 -> 5 28.8
+// and 28.0).  Two instantiations: the split as an argument cost fp32 heads 0.5 to 1 us.
+static int head_own(int L, const int *dims) {
+  long long rest = 0;
+  for (int i = 2; i < L; ++i) rest += (long long)dims[i] * dims[i + 1];
+  return rest <= 3072 ? 768 : 1024;
+}
+
 hipError_t launch_fc_head(int M, int L, const int *dims, int dtype, const void *x, const void *const *w,
                           const float *const *b, float alpha, const float *target, void *const *y, void *const *dz,
                           void *const *dx, float *const *dw, float *const *db, float *loss, void *ws,
@@ -895,6 +907,7 @@ hipError_t launch_fc_head(int M, int L, const int *dims, int dtype, const void *
   }
   hp.target = target;
   hp.loss = loss;
+  const int own = head_own(L, dims);
   const int G = N1 / V;
   const int blocks = std::min((K0 / 8 + 256 / G - 1) / (256 / G), 2 * kNumCUs);
 #define CF_HEAD_LAUNCH(DTV, TT)                                                                                    \
@@ -906,7 +919,8 @@ hipError_t launch_fc_head(int M, int L, const int *dims, int dtype, const void *
     hipLaunchKernelGGL((fc_finalize_kernel<DTV, true>), dim3((M * N1 + 15) / 16), dim3(256), 0, st, part,          \
                        pl.blocks, M * N1, (TT *)y[0], b[0], N1, alpha);                                            \
     if ((e = hipGetLastError()) != hipSuccess) return e;                                                           \
-    hipLaunchKernelGGL((fc_head_tail_kernel<DTV>), dim3(1), dim3(1024), 0, st, hp);                               \
+    hipLaunchKernelGGL((own == 768 ? fc_head_tail_kernel<DTV, 768> : fc_head_tail_kernel<DTV, 1024>), dim3(1),     \
+                       dim3(1024), 0, st, hp);                                                                     \
     if ((e = hipGetLastError()) != hipSuccess) return e;                                                           \
     switch (G) {                                                                                                   \
       case 8: hipLaunchKernelGGL((fc_head_bwd1_kernel<DTV, 8>), dim3(blocks), dim3(256), 0, st, (const TT *)x,     \

@@ -200,6 +200,15 @@ def test_head_one_call(dt, m, dims):
     assert dfeat.data_ptr() == h.dx[0].data_ptr()
 
 
+# the later layers' weights by four waves up to 3072 of them, by all beyond; more biases than four waves have threads
+@pytest.mark.parametrize("dt,m,dims", [("f32", 1, [520, 64, 47, 64, 1]), ("bf16", 2, [520, 64, 47, 64, 1]),
+                                       ("f32", 8, [520, 64, 48, 64, 5]), ("bf16", 1, [520, 64, 48, 64, 5]),
+                                       ("f32", 1, [264, 64, 96, 96, 1]), ("bf16", 3, [264, 64, 33, 130, 2]),
+                                       ("f32", 2, [264, 32, 480, 1]), ("bf16", 1, [264, 64, 230, 4])])
+def test_head_one_call_weight_loads(dt, m, dims):
+    test_head_one_call(dt, m, dims)
+
+
 @pytest.mark.parametrize("dt", DTYPES)
 def test_head_one_call_matches_per_layer_calls(dt):
     """The first layer's y is bitwise the per-layer calls' (same split-K sums,
