@@ -980,7 +980,9 @@ double tile_load(const DirParams &p, int bm, int ny) {
 // 20 x 20 x 22, 275 tiles 27.9 (64 rows 22.5), 30 x 22 x 22 batch 2, 908 tiles 52.9
 // (128 rows 40.4); stride 2, 64 -> 64 3^3 on 20 x 19 x 14 batch 2, 32 rows 8.3 (16 rows
 // 9.0, 64 rows 10.6).
-// CF_DIRECT_TILE="fm,wm,wk" and CF_DIRECT_PF force a variant (tests cover
+// A stored dz has left for the LDS-staged kernel where more than 32 rows would win
+// (choose_lds), so it takes the 16- and 32-row tiles alone; its wider ones serve forced
+// runs.  CF_DIRECT_TILE="fm,wm,wk" and CF_DIRECT_PF force a variant (tests cover
 // every one this way).
 DirCfg choose_cfg(DirParams &p, int fn, bool fwd, bool pooled = false) {
   static const DirCfg cand[] = {{4, 2, 2, 1}, {2, 2, 2, 1}, {4, 1, 4, 1}, {2, 1, 4, 1}, {1, 1, 4, 1}};

@@ -118,7 +118,8 @@ __global__ __launch_bounds__(256) void conv_smallc_fwd_kernel(
       const int id = od0 - p.pd + rb / HH, ih = oh0 - p.ph + rb % HH;
       hv[k] = u32x4_t{0u, 0u, 0u, 0u};
       if (e < NV && (unsigned)id < (unsigned)p.d && (unsigned)ih < (unsigned)p.h)
-        hv[k] = load_run8((const uint16_t *)x + (((long long)n * p.d + id) * p.h + ih) * p.w, ow0 - G::LEAD + v * G::VV, p.w);
+        hv[k] = load_run8((const uint16_t *)x + (((long long)n * p.d + id) * p.h + ih) * p.w,
+                          ow0 - G::LEAD + v * G::VV, p.w);
     }
 #pragma unroll
     for (int k = 0; k < NL; ++k) {

@@ -19,13 +19,14 @@
 //
 // Voxel order inside a tile: row r = 4 q + j is (h = j >> 1, w = 2 q + (j & 1))
 // and two tiles (dd = 0, 1) make the 2 x 2 x 8 voxels of four pooling windows;
-// the accumulator layout then leaves each window in one lane.  The slope ballots go to two registers
-// (even and odd voxels) by lane writes, 16 lanes to each of the four (dd, hh)
-// rows, and two byte permutes put them into the mask tensor's order.
+// the accumulator layout then leaves each window in one lane.  The slope ballots
+// go to two registers (even and odd voxels) by lane writes, 16 lanes to each of
+// the four (dd, hh) rows, and two byte permutes put them into the mask tensor's
+// order.
 //
 // Persistent workgroups (four per compute unit: 39.8 KB of LDS in bf16, 37.5 in
-// fp32, and at most 128 registers each) form the weight fragments once; tiles go to the XCDs in
-// contiguous runs.
+// fp32, and at most 128 registers each) form the weight fragments once; tiles go
+// to the XCDs in contiguous runs.
 // Bound by vector issue (45 instructions per 32 voxels, and about 20 more for
 // staging) beside the MFMAs in bf16, by the matrix core in fp32.  256^3 batch 2
 // bf16: 926 us with the general kernel's element gathers, 211-233 us here

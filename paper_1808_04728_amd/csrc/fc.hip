@@ -924,13 +924,13 @@ hipError_t launch_fc_head(int M, int L, const int *dims, int dtype, const void *
     if ((e = hipGetLastError()) != hipSuccess) return e;                                                           \
     switch (G) {                                                                                                   \
       case 8: hipLaunchKernelGGL((fc_head_bwd1_kernel<DTV, 8>), dim3(blocks), dim3(256), 0, st, (const TT *)x,     \
-          (const TT *)dz[0], (const TT *)w[0], dw[0], (TT *)dx[0], M, K0, N1); break;                  \
-      case 16: hipLaunchKernelGGL((fc_head_bwd1_kernel<DTV, 16>), dim3(blocks), dim3(256), 0, st, (const TT *)x,     \
-          (const TT *)dz[0], (const TT *)w[0], dw[0], (TT *)dx[0], M, K0, N1); break;                  \
-      case 32: hipLaunchKernelGGL((fc_head_bwd1_kernel<DTV, 32>), dim3(blocks), dim3(256), 0, st, (const TT *)x,     \
-          (const TT *)dz[0], (const TT *)w[0], dw[0], (TT *)dx[0], M, K0, N1); break;                  \
-      default: hipLaunchKernelGGL((fc_head_bwd1_kernel<DTV, 64>), dim3(blocks), dim3(256), 0, st, (const TT *)x,     \
-          (const TT *)dz[0], (const TT *)w[0], dw[0], (TT *)dx[0], M, K0, N1); break;                  \
+                                 (const TT *)dz[0], (const TT *)w[0], dw[0], (TT *)dx[0], M, K0, N1); break;       \
+      case 16: hipLaunchKernelGGL((fc_head_bwd1_kernel<DTV, 16>), dim3(blocks), dim3(256), 0, st, (const TT *)x,   \
+                                  (const TT *)dz[0], (const TT *)w[0], dw[0], (TT *)dx[0], M, K0, N1); break;      \
+      case 32: hipLaunchKernelGGL((fc_head_bwd1_kernel<DTV, 32>), dim3(blocks), dim3(256), 0, st, (const TT *)x,   \
+                                  (const TT *)dz[0], (const TT *)w[0], dw[0], (TT *)dx[0], M, K0, N1); break;      \
+      default: hipLaunchKernelGGL((fc_head_bwd1_kernel<DTV, 64>), dim3(blocks), dim3(256), 0, st, (const TT *)x,   \
+                                  (const TT *)dz[0], (const TT *)w[0], dw[0], (TT *)dx[0], M, K0, N1); break;      \
     }                                                                                                              \
     return hipGetLastError();                                                                                      \
   }
