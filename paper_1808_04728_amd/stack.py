@@ -37,9 +37,14 @@ def _t(dtype):
 #: 277 / 285, 112^3 batch 3 (119) 310 / 309, 120^3 batch 3 (146) 325 / 322, 96^3 batch
 #: 8 (200) 407 / 399, 144^3 batch 4 (338) 637 / 632, 128^3 batch 8 (475) 687 / 680).
 #: FLOPs stand for the device time that hides the host's; between 0.12 and 0.2
-#: TFLOP both ways are within 2%.  Single layers differ more either way: the 32 -> 64
-#: VALID layer on 31^3 batch 8 (138) 335 / 343 and on 32^3 (153) 375 / 391, 64 -> 64 on
-#: 13^3 batch 4 65 / 73, on 32^3 batch 8 (174) 667 / 628.
+#: TFLOP both ways are within 2%.  Single layers differ more and have no such line (84 of
+#: 0.2 to 350 GFLOP): below 20 GFLOP one stream is faster (64 -> 64 on 13^3 batch 4 59 /
+#: 69, 32 -> 64 stride 2 on 16^3 batch 8 43 / 74), pooled ones gain nothing from two above
+#: it either (32 -> 64 VALID on 28^3 batch 8 (98) 269 / 288, on 32^3 (153) 377 / 393),
+#: unpooled ones go either way: 64 -> 64 on 20^3 batch 8 (43) 168 / 180, on 24^3 (73) 321 /
+#: 337, but on 28^3 (117) 487 / 450 and on 32^3 (174) 668 / 629; 128 -> 128 on 13^3 batch 4
+#: (23) 152 / 135, on 16^3 (43) 174 / 186.  A program with one such layer can set
+#: overlap_wgrad itself.
 OVERLAP_FLOPS = 1.4e11
 
 
