@@ -945,7 +945,11 @@ long long count_tiles(const DirParams &p, int bm) {
 // ny column blocks: whole rounds of workgroups where all tiles are alike; with
 // several stride classes the longest tile, or the average where that is more, with a
 // share of the longest tile for the end of the launch
-double tile_load(const DirParams &p, int bm, int ny) {
+struct TileLoad {
+  double load, longest, avg, rounds;
+};
+
+TileLoad tile_load(const DirParams &p, int bm, int ny) {
   double sum = 0.0, longest = 0.0;
   long long tiles = 0;
   for (int c = 0; c < p.ncls; ++c) {
@@ -955,8 +959,27 @@ double tile_load(const DirParams &p, int bm, int ny) {
     tiles += t * ny;
     sum += (double)(t * ny) * steps;
   }
-  if (p.ncls == 1) return (double)((tiles + kNumCUs - 1) / kNumCUs) * longest;
-  return sum <= kNumCUs * longest ? longest : sum / kNumCUs + 0.25 * longest;
+  const double rounds = (double)((tiles + kNumCUs - 1) / kNumCUs);
+  const double load = p.ncls == 1 ? rounds * longest
+                      : sum <= kNumCUs * longest ? longest
+                                                 : sum / kNumCUs + 0.25 * longest;
+  return {load, longest, tiles > 0 ? sum / tiles : 0.0, rounds};
+}
+
+// Several stride classes, 64 channels or more on both sides: the first round takes the
+// longest tile's latency, every further one an average tile at the rate at which
+// workgroups that share a compute unit get on -- a fifth of that where every class has
+// a single tap, whose tiles are latency alone.  Factors against the 16-row tile's
+// latency, fitted to all five tiles of 268 calls from dz, (dy, y) and a pooled gradient;
+// on 165 others 2.0% behind the best tile on average, against 4.4% by tile_load's load.
+// 128 -> 256 3^3 stride 2 on 13 x 8 x 18 batch 2: 472 16-row tiles 21.4 us, 32 rows 13.7;
+// 64 -> 128 2^3 stride 2 on 15 x 11 x 20 batch 4 from a pooled gradient: 16 rows 6.2 us,
+// 64 rows 9.1.
+double strided_cost(const DirParams &p, const TileLoad &l, int i) {
+  static const double first[] = {3.9, 1.75, 1.45, 1.13, 1.0}, later[] = {2.7, 1.8, 1.4, 0.7, 0.6};
+  int maxtap = 0;
+  for (int c = 0; c < p.ncls; ++c) maxtap = std::max(maxtap, p.cls[c].ntap);
+  return l.longest * first[i] + (maxtap == 1 ? 0.2 : 1.0) * (l.rounds - 1.0) * l.avg * later[i];
 }
 
 // Tile choice (measured on the deep layers of the stack): the largest row
@@ -1010,10 +1033,11 @@ DirCfg choose_cfg(DirParams &p, int fn, bool fwd, bool pooled = false) {
     } else {
       const double wide[] = {3.9, 2.65, 2.1, p.ncls == 1 ? 1.27 : 1.145, 1.0};
       const double narrow[] = {5.1, 2.53, 2.9, pooled ? 1.25 : 1.41, 1.0};
+      const double *step = p.sc <= 32 ? narrow : wide;
       double best = 0.0;
       for (int i = 4; i >= 0; --i) {
-        const double cost =
-            tile_load(p, 16 * cand[i].fm * cand[i].wm, ny) * (p.sc > 32 ? wide[i] : narrow[i]);
+        const TileLoad l = tile_load(p, 16 * cand[i].fm * cand[i].wm, ny);
+        const double cost = p.ncls > 1 && p.sc > 32 && fn == 4 ? strided_cost(p, l, i) : l.load * step[i];
         if (i == 4 || cost < best) {
           best = cost;
           pick = cand[i];

@@ -323,6 +323,10 @@ STEPS = [
     ("pool", 1, (16, 32, 32), 64, 64, 2, 1, "4,1,4"),  # 256 64-row tiles
     ("pool", 1, (16, 32, 34), 64, 64, 2, 1, "lds64"),
     ("pool", 1, (24, 24, 16), 32, 64, 4, 2, "2,1,4"),
+    ("dz", 2, (13, 8, 18), 128, 256, 3, 2, "2,1,4"),   # classes of 1 to 8 taps, 472 16-row tiles
+    ("dz", 1, (5, 7, 9), 128, 256, 3, 2, "1,1,4"),     # one round of them
+    ("dy", 2, (11, 10, 24), 64, 128, 2, 2, "1,1,4"),   # classes of one tap
+    ("pool", 4, (15, 11, 20), 64, 128, 2, 2, "1,1,4"),
 ]
 
 
